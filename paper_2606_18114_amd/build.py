@@ -28,11 +28,13 @@ OBJ = os.path.join(ROOT, "_build")
 
 SOURCES = [
     "abi.cpp",
+    "abi_parts.cpp",
     "ternarize_pack.hip",
     "tgemm_fwd.hip",
     "tgemm_bwd_dx.hip",
     "tgemm_bwd_dx_f16.hip",
     "tgemm_bwd_dw.hip",
+    "tile_parts.hip",
     "tgemv.hip",
     "tgemv_b16.hip",
     "dgemv.hip",

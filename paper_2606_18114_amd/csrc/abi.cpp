@@ -1,116 +1,19 @@
 // C ABI of the ternary linear library: argument checks, then one launcher.
 // Every check runs on the host before any HIP call, so a rejected call
 // enqueues nothing (and can be exercised on a machine without a GPU).
-#include <cmath>
-#include <cstdint>
-
-#include "../../include/tmamba.h"
-#include "launchers.hpp"
+#include "abi_checks.hpp"
 
 namespace {
 
-struct Span {
-  uintptr_t lo = 0, hi = 0;  // [lo, hi)
-};
+using namespace tmk_abi;
 
-bool bytes_of(int64_t a, int64_t b, int64_t elem, int64_t* out) {
-  int64_t t;
-  if (a < 0 || b < 0) return false;
-  if (__builtin_mul_overflow(a, b, &t)) return false;
-  if (__builtin_mul_overflow(t, elem, &t)) return false;
-  if (t > (int64_t(1) << 46)) return false;  // 64 TiB: far beyond any device
-  *out = t;
-  return true;
-}
-
-Span span(const void* p, int64_t bytes) {
-  Span s;
-  s.lo = reinterpret_cast<uintptr_t>(p);
-  s.hi = s.lo + static_cast<uintptr_t>(bytes);
-  return s;
-}
-
-bool overlap(Span a, Span b) {
-  if (a.lo == 0 || b.lo == 0 || a.hi == a.lo || b.hi == b.lo) return false;
-  return a.lo < b.hi && b.lo < a.hi;
-}
-
-bool aligned(const void* p, uintptr_t a) { return (reinterpret_cast<uintptr_t>(p) % a) == 0; }
-
-bool group_ok(int32_t g) { return g == 32 || g == 64 || g == 128 || g == 256 || g == 512; }
-
-tm_status shape_kg(int64_t K, int32_t g) {
-  if (!group_ok(g)) return TM_ESHAPE;
-  if (K < 1 || K % g != 0 || K % 64 != 0) return TM_ESHAPE;
-  return TM_OK;
-}
-
-tm_status hip_status(hipError_t e) { return e == hipSuccess ? TM_OK : TM_EHIP; }
-
-hipStream_t to_hip(tm_stream s) { return reinterpret_cast<hipStream_t>(s); }
-
-constexpr int64_t kMaxGridBlocks = (int64_t(1) << 31) - 1;
-
-// Y holds es-byte elements: 4 (float32) or 2 (bfloat16 bits)
-// workspace NULL: the calls without one (cut tiles add with atomics)
-tm_status tgemm_fwd_checked(const uint16_t* X, const uint8_t* codes, const float* scales,
-                            int64_t M, int64_t N, int64_t K, int32_t g, void* Y, int es,
-                            void* workspace, int64_t workspace_bytes, tm_stream stream) {
-  if (!X || !codes || !scales || !Y) return TM_EINVAL;
-  if (M < 1 || N < 1) return TM_ESHAPE;
-  if (tm_status st = shape_kg(K, g)) return st;
-  int64_t xb, cb, sb, yb;
-  if (!bytes_of(M, K, 2, &xb) || !bytes_of(N, K / 4, 1, &cb) || !bytes_of(N, K / g, 4, &sb) ||
-      !bytes_of(M, N, es, &yb))
-    return TM_ESHAPE;
-  if (((M + 255) / 256) * ((N + 255) / 256) > kMaxGridBlocks) return TM_ESHAPE;
-  if (K > (int64_t(1) << 22) || N > (int64_t(1) << 26)) return TM_ESHAPE;  // 32-bit tile offsets
-  if (!aligned(X, 16) || !aligned(codes, 16) || !aligned(scales, 4) || !aligned(Y, 16))
-    return TM_EALIGN;
-  const Span y = span(Y, yb);
-  if (overlap(y, span(X, xb)) || overlap(y, span(codes, cb)) || overlap(y, span(scales, sb)))
-    return TM_EINVAL;
-  if (workspace) {
-    if (workspace_bytes < tm_tgemm_fwd_workspace()) return TM_ESHAPE;
-    if (!aligned(workspace, 4)) return TM_EALIGN;
-    const Span w = span(workspace, tm_tgemm_fwd_workspace());
-    if (overlap(w, y) || overlap(w, span(X, xb)) || overlap(w, span(codes, cb)) ||
-        overlap(w, span(scales, sb)))
-      return TM_EINVAL;
-  }
+tm_status tgemm_fwd_run(const uint16_t* X, const uint8_t* codes, const float* scales, int64_t M,
+                        int64_t N, int64_t K, int32_t g, void* Y, int es, void* workspace,
+                        int64_t workspace_bytes, tm_stream stream) {
+  if (tm_status st = fwd_checked(X, codes, scales, M, N, K, g, Y, es, workspace, workspace_bytes))
+    return st;
   return hip_status(tmk::launch_tgemm_fwd(X, codes, scales, M, N, K, g, Y, es == 2,
                                           static_cast<uint32_t*>(workspace), to_hip(stream)));
-}
-
-// argument checks of both dX calls; workspace NULL: the two-pass call,
-// which takes none
-tm_status bwd_dx_checked(const uint16_t* dY, const uint8_t* codes, const float* scales,
-                         int64_t M, int64_t N, int64_t K, int32_t g, float* dX,
-                         const void* workspace, int64_t workspace_bytes) {
-  if (!dY || !codes || !scales || !dX) return TM_EINVAL;
-  if (M < 1 || N < 1 || N % 8 != 0) return TM_ESHAPE;
-  if (tm_status st = shape_kg(K, g)) return st;
-  if (N > (int64_t(1) << 22) || K > (int64_t(1) << 26)) return TM_ESHAPE;
-  int64_t yb, cb, sb, xb;
-  if (!bytes_of(M, N, 2, &yb) || !bytes_of(N, K / 4, 1, &cb) || !bytes_of(N, K / g, 4, &sb) ||
-      !bytes_of(M, K, 4, &xb))
-    return TM_ESHAPE;
-  if (((M + 255) / 256) * ((K + 255) / 256) > kMaxGridBlocks) return TM_ESHAPE;
-  if (!aligned(dY, 16) || !aligned(codes, 16) || !aligned(scales, 4) || !aligned(dX, 16))
-    return TM_EALIGN;
-  const Span o = span(dX, xb);
-  if (overlap(o, span(dY, yb)) || overlap(o, span(codes, cb)) || overlap(o, span(scales, sb)))
-    return TM_EINVAL;
-  if (workspace) {
-    const int64_t need = tmk::dx_f16_workspace_bytes(M, N);
-    if (workspace_bytes < need) return TM_ESHAPE;
-    if (!aligned(workspace, 256)) return TM_EALIGN;
-    const Span w = span(workspace, need);
-    if (overlap(w, o) || overlap(w, span(dY, yb)) || overlap(w, span(codes, cb)) ||
-        overlap(w, span(scales, sb)))
-      return TM_EINVAL;
-  }
-  return TM_OK;
 }
 
 // batches of 9 .. 16 rows at g >= 64 go to the bfloat16 matrix-core form
@@ -305,23 +208,22 @@ tm_status tm_scale_ste_grad(const float* W, const uint8_t* codes, const float* s
 
 tm_status tm_tgemm_fwd(const uint16_t* X, const uint8_t* codes, const float* scales, int64_t M,
                        int64_t N, int64_t K, int32_t g, float* Y, tm_stream stream) {
-  return tgemm_fwd_checked(X, codes, scales, M, N, K, g, Y, 4, nullptr, 0, stream);
+  return tgemm_fwd_run(X, codes, scales, M, N, K, g, Y, 4, nullptr, 0, stream);
 }
 
-int64_t tm_tgemm_fwd_workspace(void) { return 8 * (int64_t)tmk::kFwdMaxTicketTiles; }
+int64_t tm_tgemm_fwd_workspace(void) { return kFwdTicketBytes; }
 
 tm_status tm_tgemm_fwd_ws(const uint16_t* X, const uint8_t* codes, const float* scales,
                           int64_t M, int64_t N, int64_t K, int32_t g, float* Y, void* workspace,
                           int64_t workspace_bytes, tm_stream stream) {
   if (!workspace) return TM_EINVAL;
-  return tgemm_fwd_checked(X, codes, scales, M, N, K, g, Y, 4, workspace, workspace_bytes,
-                           stream);
+  return tgemm_fwd_run(X, codes, scales, M, N, K, g, Y, 4, workspace, workspace_bytes, stream);
 }
 
 tm_status tm_tgemm_fwd_bf16(const uint16_t* X, const uint8_t* codes, const float* scales,
                             int64_t M, int64_t N, int64_t K, int32_t g, uint16_t* Y,
                             tm_stream stream) {
-  return tgemm_fwd_checked(X, codes, scales, M, N, K, g, Y, 2, nullptr, 0, stream);
+  return tgemm_fwd_run(X, codes, scales, M, N, K, g, Y, 2, nullptr, 0, stream);
 }
 
 tm_status tm_tgemm_bwd_dx(const uint16_t* dY, const uint8_t* codes, const float* scales,
@@ -350,17 +252,7 @@ tm_status tm_tgemm_bwd_dx_f16(const uint16_t* dY, const uint8_t* codes, const fl
 
 tm_status tm_tgemm_bwd_dw_ste(const uint16_t* dY, const uint16_t* X, int64_t M, int64_t N,
                               int64_t K, float* dW, int32_t accumulate, tm_stream stream) {
-  if (!dY || !X || !dW) return TM_EINVAL;
-  if (accumulate != 0 && accumulate != 1) return TM_EINVAL;
-  if (M < 1 || N < 1 || N % 8 != 0 || K < 1 || K % 64 != 0) return TM_ESHAPE;
-  int64_t yb, xb, wb;
-  if (!bytes_of(M, N, 2, &yb) || !bytes_of(M, K, 2, &xb) || !bytes_of(N, K, 4, &wb))
-    return TM_ESHAPE;
-  if (((N + 255) / 256) * ((K + 255) / 256) * ((M + 255) / 256) > kMaxGridBlocks) return TM_ESHAPE;
-  if (N > (int64_t(1) << 26) || K > (int64_t(1) << 26)) return TM_ESHAPE;  // 32-bit row offsets
-  if (!aligned(dY, 16) || !aligned(X, 16) || !aligned(dW, 16)) return TM_EALIGN;
-  const Span o = span(dW, wb);
-  if (overlap(o, span(dY, yb)) || overlap(o, span(X, xb))) return TM_EINVAL;
+  if (tm_status st = bwd_dw_checked(dY, X, M, N, K, dW, accumulate)) return st;
   return hip_status(tmk::launch_tgemm_bwd_dw(dY, X, M, N, K, dW, accumulate, to_hip(stream)));
 }
 

@@ -62,6 +62,23 @@ hipError_t launch_tgemm_bwd_dx_f16(const uint16_t* dY, const uint8_t* codes, con
                                    void* workspace, hipStream_t stream);
 hipError_t launch_tgemm_bwd_dw(const uint16_t* dY, const uint16_t* X, int64_t M, int64_t N,
                                int64_t K, float* dW, int accumulate, hipStream_t stream);
+// The same three with the parts of cut tiles meeting in slots (tile_parts.hpp):
+// slots NULL, or the *_slot_bytes of the shape (0: no tile is cut); dX also
+// rounded once to bfloat16 (then slots are needed where a tile is cut), and
+// dY in float32 (f32_in; its bfloat16 rounding is written to dYb).
+int64_t bwd_dx_slot_bytes(int64_t M, int64_t N, int64_t K);
+int64_t bwd_dx_f16_slot_bytes(int64_t M, int64_t N, int64_t K);
+int64_t bwd_dw_slot_bytes(int64_t M, int64_t N, int64_t K);
+hipError_t launch_tgemm_bwd_dx_parts(const uint16_t* dY, const uint8_t* codes,
+                                     const float* scales, int64_t M, int64_t N, int64_t K, int g,
+                                     void* dX, bool bf16_out, float* slots, hipStream_t stream);
+hipError_t launch_tgemm_bwd_dx_f16_parts(const void* dY, bool f32_in, uint16_t* dYb,
+                                         const uint8_t* codes, const float* scales, int64_t M,
+                                         int64_t N, int64_t K, int g, void* dX, bool bf16_out,
+                                         void* workspace, float* slots, hipStream_t stream);
+hipError_t launch_tgemm_bwd_dw_parts(const uint16_t* dY, const uint16_t* X, int64_t M, int64_t N,
+                                     int64_t K, float* dW, int accumulate, float* slots,
+                                     hipStream_t stream);
 // dst[0 .. n) = 0 (float32), by a plain fill kernel
 hipError_t launch_fill_zero_f32(float* dst, int64_t n, hipStream_t stream);
 // zeroes tiles t0 .. t0 + count - 1 of a float32 [rows, cols] array dealt in

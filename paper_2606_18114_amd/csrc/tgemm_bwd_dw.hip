@@ -20,10 +20,10 @@
 //
 // Work split (persistent, one workgroup per CU): the T output tiles are
 // dealt round-robin, whole, T / P per workgroup; the T % P remaining tiles
-// are each cut along the tokens into P / (T % P) parts that are added into
-// dW with float32 atomics (dW is cleared first unless accumulating), so
-// every CU does the same work.  Whole tiles are written with plain stores
-// (read-add-write when accumulating).
+// are cut along the tokens into parts that meet in slots of a caller's
+// buffer (tile_parts.hpp), or, without one, by float32 atomics into a
+// cleared dW.  Whole tiles are written with plain stores (read-add-write
+// when accumulating).
 //
 // The direct-to-LDS loads are issued from inline assembly, so the compiler
 // neither tracks nor waits for them; each wave issues exactly eight per
@@ -32,6 +32,8 @@
 
 #include "common.hpp"
 #include "launchers.hpp"
+#include "tile_parts.hpp"
+#include "tile_store.hpp"
 
 namespace tmk {
 
@@ -88,22 +90,22 @@ __device__ __forceinline__ uint32_t dw_off(int r, int c) {
   return (uint32_t)(r * 512 + 32 * ((c >> 4) ^ dw_swz(r)) + 2 * (c & 15));
 }
 
+// ADD: dW may be added to (accumulate, or parts without slots); the plain form
+// only stores, so its accumulators feed one kind of output and do not spill
+template <bool ADD>
 __global__ __launch_bounds__(256) void tgemm_bwd_dw_kernel(
     const uint16_t* __restrict__ dY, const uint16_t* __restrict__ X, int64_t M, int64_t N,
-    int64_t K, float* __restrict__ dW, int accumulate, uint32_t tiles_k, uint32_t ntiles,
-    uint32_t parts) {
+    int64_t K, float* __restrict__ dW, int accumulate, uint32_t tiles_k, uint32_t full,
+    uint32_t rem, uint32_t parts, int per, float* __restrict__ slots) {
   __shared__ __attribute__((aligned(1024))) uint8_t lds[kDwLds];
 
   const int lane = threadIdx.x & 63;
   const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   const int wy = wave >> 1, wx = wave & 1;  // 128-row (N) and 128-column (K) halves
-  const int l32 = lane & 31;
   const int g = lane >> 4;                  // 16-lane group of the transpose reads
   const int j16 = lane & 15;
   const uint32_t P = gridDim.x;
   const uint32_t bid = xcd_remap(blockIdx.x, P);
-  const uint32_t full = ntiles / P;         // whole tiles per workgroup
-  const uint32_t rem = ntiles % P;          // tiles cut into `parts` token ranges
   const int nst = (int)((M + kDwBM - 1) / kDwBM);
   const uint32_t lds0 = (uint32_t)(uintptr_t)lds;
 
@@ -122,14 +124,15 @@ __global__ __launch_bounds__(256) void tgemm_bwd_dw_kernel(
       s_beg = 0;
       s_end = nst;
       whole = true;
-    } else if (item == full && rem != 0 && bid < rem * parts) {
-      tile = full * P + bid / parts;
-      const uint32_t part = bid % parts;
-      const int per = (nst + (int)parts - 1) / (int)parts;
+    } else if (item == full && bid < rem * parts) {
+      // part bid / rem of leftover tile bid % rem
+      // (the quotients are computed in vector registers: the loaders need
+      // them in scalar ones)
+      const uint32_t part = (uint32_t)__builtin_amdgcn_readfirstlane((int)(bid / rem));
+      tile = full * P + (bid - part * rem);
       s_beg = (int)part * per;
       s_end = s_beg + per < nst ? s_beg + per : nst;
-      whole = false;
-      if (s_beg >= s_end) break;
+      whole = parts == 1;
     } else {
       break;
     }
@@ -140,6 +143,7 @@ __global__ __launch_bounds__(256) void tgemm_bwd_dw_kernel(
     // stage, 2 rows (1 KiB) per load; lane -> row 2J + lane/32, 16-byte piece
     // lane%32 of the LDS row, holding logical piece lp (unit-permuted)
     uint32_t ycol[4], xcol[4];  // byte offsets of this lane's columns in a row
+    uint32_t yrow[4], xrow[4];  // and of its rows in a stage
     const int r_lo = lane >> 5;   // row of load i: 2 (4 wave + i) + r_lo
 #pragma unroll
     for (int i = 0; i < 4; ++i) {
@@ -152,28 +156,39 @@ __global__ __launch_bounds__(256) void tgemm_bwd_dw_kernel(
       ck = ck < K ? ck : K - 8;
       ycol[i] = (uint32_t)cn * 2u;
       xcol[i] = (uint32_t)ck * 2u;
+      yrow[i] = (uint32_t)r * (uint32_t)N * 2u;
+      xrow[i] = (uint32_t)r * (uint32_t)K * 2u;
     }
-    auto dma = [&](int st, int slot) {
+    struct DmaStage {
+      const uint8_t *yb, *xb;
+      uint32_t ylast, xlast, dst;
+    };
+    auto dma_begin = [&](int st, int slot) {
       st = st < s_end ? st : s_end - 1;  // past the range: reload its last stage
       const int64_t m0 = (int64_t)st * kDwBM;
       // rows past M re-read row M - 1 (in bounds); those tokens are zeroed in
       // the dY operand below
-      const int rows = (int)(M - m0 < kDwBM ? M - m0 : kDwBM);
-      const uint8_t* yb = reinterpret_cast<const uint8_t*>(dY + m0 * N);
-      const uint8_t* xb = reinterpret_cast<const uint8_t*>(X + m0 * K);
-      const uint32_t dst = lds0 + slot * kDwSlot;
-#pragma unroll
-      for (int i = 0; i < 4; ++i) {
-        int r = 2 * (wave * 4 + i) + r_lo;
-        r = r < rows ? r : rows - 1;
-        dw_dma16(yb, (uint32_t)(r * N) * 2u + ycol[i], dst + 1024 * (wave * 4 + i));
-      }
-#pragma unroll
-      for (int i = 0; i < 4; ++i) {
-        int r = 2 * (wave * 4 + i) + r_lo;
-        r = r < rows ? r : rows - 1;
-        dw_dma16(xb, (uint32_t)(r * K) * 2u + xcol[i], dst + kDwOp + 1024 * (wave * 4 + i));
-      }
+      const uint32_t last = (uint32_t)(M - m0 < kDwBM ? M - m0 : kDwBM) - 1u;
+      DmaStage d;
+      d.yb = reinterpret_cast<const uint8_t*>(dY + m0 * N);
+      d.xb = reinterpret_cast<const uint8_t*>(X + m0 * K);
+      d.ylast = last * (uint32_t)N * 2u;
+      d.xlast = last * (uint32_t)K * 2u;
+      d.dst = lds0 + slot * kDwSlot + 4096u * wave;
+      return d;
+    };
+    // load J of the eight of a stage: dY rows (0-3), X rows (4-7)
+    auto dma_piece = [&](const DmaStage& d, auto j_tag) {
+      constexpr int J = decltype(j_tag)::value, i = J % 4;
+      if constexpr (J < 4)
+        dw_dma16(d.yb, (yrow[i] < d.ylast ? yrow[i] : d.ylast) + ycol[i], d.dst + 1024 * i);
+      else
+        dw_dma16(d.xb, (xrow[i] < d.xlast ? xrow[i] : d.xlast) + xcol[i],
+                 d.dst + kDwOp + 1024 * i);
+    };
+    auto dma = [&](int st, int slot) {
+      const DmaStage d = dma_begin(st, slot);
+      dw_static_for<0, kDwLoads>([&](auto j_tag) { dma_piece(d, j_tag); });
     };
 
     f32x16 acc[4][4];
@@ -184,10 +199,10 @@ __global__ __launch_bounds__(256) void tgemm_bwd_dw_kernel(
 #pragma unroll
         for (int i = 0; i < 16; ++i) acc[a][b][i] = 0.f;
 
-    // prologue: stages s_beg .. s_beg + 2 in flight
+    // prologue: stages s_beg .. s_beg + 2 in flight, the first two landed
 #pragma unroll
     for (int p = 0; p < kDwRing - 1; ++p) dma(s_beg + p, p);
-    dw_stage_barrier<2 * kDwLoads>();
+    dw_stage_barrier<kDwLoads>();
 
     // per-lane byte offsets of the transpose reads of block a (dY) / b (X)
     // inside a stage's operand tile, token rows trow .. (the reads of token
@@ -197,30 +212,65 @@ __global__ __launch_bounds__(256) void tgemm_bwd_dw_kernel(
     for (int a = 0; a < 4; ++a) aoff[a] = dw_off(trow, wy * 128 + 32 * a + tcol);
 #pragma unroll
     for (int b = 0; b < 4; ++b) boff[b] = kDwOp + dw_off(trow, wx * 128 + 32 * b + tcol);
+    auto frag = [&](const uint8_t* sb, uint32_t off, int t) {
+      const s16x4 lo = __builtin_amdgcn_ds_read_tr16_b64_v4i16(
+          (lds_s16x4*)(sb + off + 16 * t * 512));
+      const s16x4 hi = __builtin_amdgcn_ds_read_tr16_b64_v4i16(
+          (lds_s16x4*)(sb + off + (16 * t + 4) * 512));
+      const u32x2 l = __builtin_bit_cast(u32x2, lo), u = __builtin_bit_cast(u32x2, hi);
+      return u32x4{l.x, l.y, u.x, u.y};
+    };
+    // operands of the two 16-token steps of a stage; read X of a step in the
+    // order its MFMAs first use them
+    u32x4 af[2][4], bf[2][4];
+    auto read_op = [&](const uint8_t* sb, auto t_tag, auto x_tag) {
+      constexpr int T = decltype(t_tag)::value, X_ = decltype(x_tag)::value;
+      if constexpr (X_ == 0)
+        af[T][0] = frag(sb, aoff[0], T);
+      else if constexpr (X_ < 5)
+        bf[T][X_ - 1] = frag(sb, boff[X_ - 1], T);
+      else
+        af[T][X_ - 4] = frag(sb, aoff[X_ - 4], T);
+    };
 
-    // One stage in ring slot SLOT (a compile-time constant, so every LDS
-    // address below is a register plus an immediate offset).
+    // One full stage in ring slot SLOT (a compile-time constant, so every LDS
+    // address is a register plus an immediate offset).  One wave per SIMD
+    // issues everything, so the order is fixed by hand, one MFMA per slot
+    // fenced by sched_barrier: the first step's operands were read during
+    // the stage before; its 16 MFMAs cover the reads of the second step (even
+    // slots) and the eight loads of stage st + 3 (odd slots), and the second
+    // step's MFMAs the first reads of stage st + 1.  No MFMA waits for an LDS
+    // read issued less than two MFMAs earlier.
     auto stage = [&](auto slot_tag, int st) {
       constexpr int SLOT = decltype(slot_tag)::value;
       const uint8_t* sb = lds + SLOT * kDwSlot;
-      // tokens of this stage past M contribute nothing (their dY rows are
-      // zeroed in the operand); the check is uniform and true at most once
+      const uint8_t* nb = lds + ((SLOT + 1) & (kDwRing - 1)) * kDwSlot;
+      const DmaStage d = dma_begin(st + kDwRing - 1, (SLOT + kDwRing - 1) & (kDwRing - 1));
+      dw_static_for<0, 32>([&](auto k_tag) {
+        constexpr int k = decltype(k_tag)::value;
+        constexpr int t = k / 16, a = (k % 16) / 4, b = k % 4;
+        acc[a][b] = mfma32(as_bf16x8(af[t][a]), as_bf16x8(bf[t][b]), acc[a][b]);
+        if constexpr (k % 2 == 0)
+          read_op(t == 0 ? sb : nb, std::integral_constant<int, 1 - t>{},
+                  std::integral_constant<int, (k % 16) / 2>{});
+        else if constexpr (k < 16)
+          dma_piece(d, std::integral_constant<int, k / 2>{});
+        __builtin_amdgcn_sched_barrier(0);
+      });
+    };
+    // the same without the overlap, for the last stages: tokens past M
+    // contribute nothing (their dY values are zeroed in the operand)
+    auto stage_tail = [&](auto slot_tag, int st) {
+      constexpr int SLOT = decltype(slot_tag)::value;
+      const uint8_t* sb = lds + SLOT * kDwSlot;
       const int64_t mvalid = M - (int64_t)st * kDwBM;
-      auto frag = [&](uint32_t off, int t) {
-        const s16x4 lo = __builtin_amdgcn_ds_read_tr16_b64_v4i16(
-            (lds_s16x4*)(sb + off + 16 * t * 512));
-        const s16x4 hi = __builtin_amdgcn_ds_read_tr16_b64_v4i16(
-            (lds_s16x4*)(sb + off + (16 * t + 4) * 512));
-        const u32x2 l = __builtin_bit_cast(u32x2, lo), u = __builtin_bit_cast(u32x2, hi);
-        return u32x4{l.x, l.y, u.x, u.y};
-      };
 #pragma unroll
       for (int t = 0; t < kDwBM / 16; ++t) {
-        u32x4 af[4], bf[4];
+        u32x4 ta[4], tb[4];
 #pragma unroll
-        for (int a = 0; a < 4; ++a) af[a] = frag(aoff[a], t);
+        for (int a = 0; a < 4; ++a) ta[a] = frag(sb, aoff[a], t);
 #pragma unroll
-        for (int b = 0; b < 4; ++b) bf[b] = frag(boff[b], t);
+        for (int b = 0; b < 4; ++b) tb[b] = frag(sb, boff[b], t);
         if (mvalid < kDwBM) {
           // this lane's tokens: 16 t + 8 (g / 2) + e, e = 0 .. 7 (pairs per dword)
           const int base = 16 * t + 8 * (g >> 1);
@@ -231,7 +281,7 @@ __global__ __launch_bounds__(256) void tgemm_bwd_dw_kernel(
               const int m_lo = base + 2 * e;
               const uint32_t keep =
                   (m_lo < mvalid ? 0x0000FFFFu : 0u) | (m_lo + 1 < mvalid ? 0xFFFF0000u : 0u);
-              af[a][e] &= keep;
+              ta[a][e] &= keep;
             }
           }
         }
@@ -239,53 +289,53 @@ __global__ __launch_bounds__(256) void tgemm_bwd_dw_kernel(
         for (int a = 0; a < 4; ++a)
 #pragma unroll
           for (int b = 0; b < 4; ++b)
-            acc[a][b] = mfma32(as_bf16x8(af[a]), as_bf16x8(bf[b]), acc[a][b]);
+            acc[a][b] = mfma32(as_bf16x8(ta[a]), as_bf16x8(tb[b]), acc[a][b]);
       }
     };
 
-    // groups of kDwRing stages (the stages past s_end only load and wait)
-    for (int st0 = s_beg; st0 < s_end; st0 += kDwRing) {
+    // groups of kDwRing full stages, then the rest
+    const int s_full = s_end < nst || M % kDwBM == 0 ? s_end : s_end - 1;
+    int st0 = s_beg;
+    if (st0 + kDwRing <= s_full)
+      dw_static_for<0, 8>([&](auto x_tag) {
+        read_op(lds, std::integral_constant<int, 0>{}, x_tag);
+      });
+    for (; st0 + kDwRing <= s_full; st0 += kDwRing) {
+      dw_static_for<0, kDwRing>([&](auto i_tag) {
+        stage(i_tag, st0 + decltype(i_tag)::value);
+        dw_stage_barrier<kDwLoads>();
+      });
+    }
+    for (; st0 < s_end; st0 += kDwRing) {  // (the stages past s_end only load and wait)
       dw_static_for<0, kDwRing>([&](auto i_tag) {
         constexpr int i = decltype(i_tag)::value;
         const int st = st0 + i;
         dma(st + kDwRing - 1, (i + kDwRing - 1) & (kDwRing - 1));
-        if (st < s_end) stage(i_tag, st);
-        dw_stage_barrier<2 * kDwLoads>();
+        if (st < s_end) stage_tail(i_tag, st);
+        dw_stage_barrier<kDwLoads>();
       });
     }
     // every load of this item has landed before the ring is reused
     asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
     __builtin_amdgcn_s_barrier();
 
-    // ---- write: lane holds column l32 of each block, rows 8 (i/4) + 4 h + i%4
-    const int h = lane >> 5;
-    const int mode = !whole ? 2 : (accumulate ? 1 : 0);  // atomic add / add / store
-    const int kleft = (int)(K - k0 - wx * 128 - l32);      // this lane's column is valid if > 32 b
-    const uint32_t lane_off = (uint32_t)(4 * h) * (uint32_t)K + (uint32_t)l32;
-#pragma unroll
-    for (int a = 0; a < 4; ++a) {
-      const int64_t rowa = n0 + wy * 128 + 32 * a;
-      const int nleft = (int)(N - rowa) - 4 * h;  // rows 8 (i/4) + i%4 valid if below
-      float* pa = dW + rowa * K + k0 + wx * 128;  // uniform
-#pragma unroll
-      for (int b = 0; b < 4; ++b) {
-        if (kleft <= 32 * b) continue;
-#pragma unroll
-        for (int i = 0; i < 16; ++i) {
-          const int dn = 8 * (i / 4) + (i % 4);
-          if (dn < nleft) {
-            float* q = pa + 32 * b + (uint32_t)dn * (uint32_t)K + lane_off;
-            const float v = acc[a][b][i];
-            if (mode == 2)
-              atomicAdd(q, v);
-            else if (mode == 1)
-              *q += v;
-            else
-              *q = v;
-          }
-        }
-        __builtin_amdgcn_sched_barrier(0);  // one block's values live at a time
-      }
+    // ---- write
+    auto val = [&](int a, int b, int i) { return acc_value(acc[a][b][i]); };
+    auto none = [](int) {};
+    const int64_t row0 = n0 + wy * 128, col0 = k0 + wx * 128;
+    const int rows_left = (int)(N - row0 < 256 ? N - row0 : 256);
+    const int cols_left = (int)(K - col0 < 256 ? K - col0 : 256);
+    float* out = dW + row0 * K + col0;
+    if (whole && !(ADD && accumulate))
+      tile_store(out, K, rows_left, cols_left, none, val, [](float* p, float v) { *p = v; });
+    else if (!whole && (!ADD || slots))
+      slot_store(slots + (int64_t)bid * kSlotFloats, rows_left, cols_left, none, val);
+    else if constexpr (ADD) {
+      if (whole)
+        tile_store(out, K, rows_left, cols_left, none, val, [](float* p, float v) { *p += v; });
+      else
+        tile_store(out, K, rows_left, cols_left, none, val,
+                   [](float* p, float v) { atomicAdd(p, v); });
     }
   }
   asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
@@ -318,23 +368,52 @@ hipError_t launch_fill_zero_f32(float* dst, int64_t n, hipStream_t stream) {
   return hipGetLastError();
 }
 
-hipError_t launch_tgemm_bwd_dw(const uint16_t* dY, const uint16_t* X, int64_t M, int64_t N,
-                               int64_t K, float* dW, int accumulate, hipStream_t stream) {
+// Time of one group of ring stages (four, 128 tokens) of a tile, of a slot's
+// write and read, and of the reduction's launch; see plan_parts
+constexpr double kDwUnitUs = 3.6, kDwSlotUs = 0.1, kDwLaunchUs = 5.0;
+
+static TilePlan dw_plan(int64_t M, int64_t N, int64_t K) {
+  const int64_t nt = ((N + kDwTN - 1) / kDwTN) * ((K + kDwTK - 1) / kDwTK);
+  return plan_parts(nt, (M + kDwBM - 1) / kDwBM, kDwRing, current_cu_count(), kDwUnitUs,
+                    kDwSlotUs, kDwLaunchUs);
+}
+
+int64_t bwd_dw_slot_bytes(int64_t M, int64_t N, int64_t K) {
+  return dw_plan(M, N, K).slots() * kSlotBytes;
+}
+
+hipError_t launch_tgemm_bwd_dw_parts(const uint16_t* dY, const uint16_t* X, int64_t M, int64_t N,
+                                     int64_t K, float* dW, int accumulate, float* slots,
+                                     hipStream_t stream) {
   const int64_t tn = (N + kDwTN - 1) / kDwTN, tk = (K + kDwTK - 1) / kDwTK;
   const int64_t ntiles = tn * tk;
-  const int cus = current_cu_count();
-  const int64_t P = ntiles < cus ? ntiles : cus;
-  const int64_t rem = ntiles % P;
-  int64_t parts = rem ? P / rem : 1;
-  const int64_t nst = (M + kDwBM - 1) / kDwBM;
-  if (parts > nst) parts = nst;
-  if (rem && !accumulate) {  // the cut tiles (the last rem) are summed with atomics
-    const hipError_t e = launch_zero_tiles_f32(dW, N, K, tk, ntiles - rem, rem, stream);
-    if (e != hipSuccess) return e;
+  TilePlan t = dw_plan(M, N, K);
+  if (t.parts > 1 && !slots) {
+    t = plan_atomic(ntiles, (M + kDwBM - 1) / kDwBM, current_cu_count());
+    if (t.rem && t.parts > 1 && !accumulate) {  // these tiles are summed with atomics
+      const hipError_t e = launch_zero_tiles_f32(dW, N, K, tk, ntiles - t.rem, t.rem, stream);
+      if (e != hipSuccess) return e;
+    }
   }
-  hipLaunchKernelGGL(tgemm_bwd_dw_kernel, dim3((unsigned)P), dim3(256), 0, stream, dY, X, M, N,
-                     K, dW, accumulate, (uint32_t)tk, (uint32_t)ntiles, (uint32_t)parts);
-  return hipGetLastError();
+  const bool add = accumulate || (t.parts > 1 && !slots);
+#define TM_DW_CASE(ADD_)                                                                          \
+  hipLaunchKernelGGL(tgemm_bwd_dw_kernel<ADD_>, dim3((unsigned)t.grid), dim3(256), 0, stream, dY, \
+                     X, M, N, K, dW, accumulate, (uint32_t)tk, (uint32_t)t.full,                  \
+                     (uint32_t)t.rem, (uint32_t)t.parts, t.per, slots)
+  if (add)
+    TM_DW_CASE(true);
+  else
+    TM_DW_CASE(false);
+#undef TM_DW_CASE
+  const hipError_t e = hipGetLastError();
+  if (e != hipSuccess || t.parts == 1 || !slots) return e;
+  return launch_reduce_parts(slots, t.rem, t.parts, ntiles - t.rem, tk, N, K, dW, false,
+                             accumulate != 0, stream);
+}
+
+hipError_t launch_tgemm_bwd_dw(const uint16_t* dY, const uint16_t* X, int64_t M, int64_t N,
+                               int64_t K, float* dW, int accumulate, hipStream_t stream) {
+  return launch_tgemm_bwd_dw_parts(dY, X, M, N, K, dW, accumulate, nullptr, stream);
 }
 
 }  // namespace tmk

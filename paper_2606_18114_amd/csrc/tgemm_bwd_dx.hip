@@ -37,6 +37,8 @@
 // and counts them itself (vector-memory operations retire in order).
 #include "dx_common.hpp"
 #include "launchers.hpp"
+#include "tile_parts.hpp"
+#include "tile_store.hpp"
 
 namespace tmk {
 
@@ -51,11 +53,14 @@ constexpr int kDxRingBase = 2 * kDxDec;            // planes first, then the rin
 constexpr int kDxLds = kDxRingBase + kDxRing * kDxSlot;  // 140 KiB
 constexpr int kDxLoads = 7;                        // direct-to-LDS loads per wave per stage
 
-template <int G>
+// BF: dX in bfloat16 (each float32 sum rounded to nearest even once), else
+// float32; the bfloat16 form always has slots for its parts
+template <int G, bool BF>
 __global__ __launch_bounds__(256) void tgemm_bwd_dx_kernel(
     const uint16_t* __restrict__ dY, const uint32_t* __restrict__ codes,
     const float* __restrict__ scales, int64_t M, int64_t N, int64_t K,
-    float* __restrict__ dX, uint32_t tiles_k, uint32_t ntiles, uint32_t parts) {
+    void* __restrict__ dXv, uint32_t tiles_k, uint32_t full, uint32_t rem, uint32_t parts, int per,
+    float* __restrict__ slots) {
   __shared__ __attribute__((aligned(1024))) uint8_t lds[kDxLds];
   constexpr int kGpt = G < kDxTK ? kDxTK / G : 1;  // scale groups per tile row
 
@@ -69,8 +74,6 @@ __global__ __launch_bounds__(256) void tgemm_bwd_dx_kernel(
   const int j16 = lane & 15;
   const uint32_t P = gridDim.x;
   const uint32_t bid = xcd_remap(blockIdx.x, P);
-  const uint32_t full = ntiles / P;
-  const uint32_t rem = ntiles % P;
   const int nst = (int)((N + kDxBN - 1) / kDxBN);
   const int64_t kw = K / 16;                // code words per weight row
   const int64_t ng = K / G;                 // scale groups per weight row
@@ -110,14 +113,15 @@ __global__ __launch_bounds__(256) void tgemm_bwd_dx_kernel(
       s_beg = 0;
       s_end = nst;
       whole = true;
-    } else if (item == full && rem != 0 && bid < rem * parts) {
-      tile = full * P + bid / parts;
-      const uint32_t part = bid % parts;
-      const int per = (nst + (int)parts - 1) / (int)parts;
+    } else if (item == full && bid < rem * parts) {
+      // part bid / rem of leftover tile bid % rem
+      // (the quotients are computed in vector registers: the loaders need
+      // them in scalar ones)
+      const uint32_t part = (uint32_t)__builtin_amdgcn_readfirstlane((int)(bid / rem));
+      tile = full * P + (bid - part * rem);
       s_beg = (int)part * per;
       s_end = s_beg + per < nst ? s_beg + per : nst;
-      whole = false;
-      if (s_beg >= s_end) break;
+      whole = parts == 1;
     } else {
       break;
     }
@@ -432,62 +436,92 @@ __global__ __launch_bounds__(256) void tgemm_bwd_dx_kernel(
     asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
     __builtin_amdgcn_s_barrier();
 
-    // ---- write: lane holds column l32 of each block, rows 8 (i/4) + 4 h + i%4
-    const int kleft = (int)(K - k0 - wk * 128 - l32);  // column valid if > 32 b
-    const uint32_t lane_off = (uint32_t)(4 * h) * (uint32_t)K + (uint32_t)l32;
-#pragma unroll
-    for (int a = 0; a < 4; ++a) {
-      const int rowa = wm * 128 + 32 * a;
-      const int mleft = rows - rowa - 4 * h;  // rows 8 (i/4) + i%4 valid if below
-      float* pa = dX + (m0 + rowa) * K + k0 + wk * 128;  // uniform
-#pragma unroll
-      for (int b = 0; b < 4; ++b) {
-        if (kleft <= 32 * b) continue;
-#pragma unroll
-        for (int i = 0; i < 16; ++i) {
-          const int dm = 8 * (i / 4) + (i % 4);
-          if (dm < mleft) {
-            float* q = pa + 32 * b + (uint32_t)dm * (uint32_t)K + lane_off;
-            if (whole)
-              *q = acc[a][b][i];
-            else
-              atomicAdd(q, acc[a][b][i]);
-          }
-        }
-        __builtin_amdgcn_sched_barrier(0);  // one block's values live at a time
-      }
-    }
+    // ---- write
+    auto prep = [](int) {};
+    auto val = [&](int a, int b, int i) { return acc_value(acc[a][b][i]); };
+    using Out = std::conditional_t<BF, uint16_t, float>;
+    const int rows_left = rows - wm * 128;
+    const int64_t col0 = k0 + wk * 128;
+    const int cols_left = (int)(K - col0 < 256 ? K - col0 : 256);
+    Out* out = reinterpret_cast<Out*>(dXv) + (m0 + wm * 128) * K + col0;
+    if (whole)
+      tile_store(out, K, rows_left, cols_left, prep, val, [](Out* p, float v) {
+        if constexpr (BF)
+          *p = __builtin_bit_cast(uint16_t, (__bf16)v);
+        else
+          *p = v;
+      });
+    else if (BF || slots)
+      slot_store(slots + (int64_t)bid * kSlotFloats, rows_left, cols_left, prep, val);
+    else if constexpr (!BF)
+      tile_store(out, K, rows_left, cols_left, prep, val,
+                 [](float* p, float v) { atomicAdd(p, v); });
   }
   asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+}
+
+// Time of one group of ring stages (four, 128 weight rows) of a tile, of a
+// slot's write and read, and of the reduction's launch; see plan_parts
+constexpr double kDxUnitUs = 6.0, kDxSlotUs = 0.1, kDxLaunchUs = 5.0;
+
+static TilePlan dx_plan(int64_t M, int64_t N, int64_t K) {
+  const int64_t nt = ((M + kDxTM - 1) / kDxTM) * ((K + kDxTK - 1) / kDxTK);
+  return plan_parts(nt, (N + kDxBN - 1) / kDxBN, kDxRing, current_cu_count(), kDxUnitUs, kDxSlotUs,
+                    kDxLaunchUs);
+}
+
+int64_t bwd_dx_slot_bytes(int64_t M, int64_t N, int64_t K) {
+  return dx_plan(M, N, K).slots() * kSlotBytes;
+}
+
+hipError_t launch_tgemm_bwd_dx_parts(const uint16_t* dY, const uint8_t* codes,
+                                     const float* scales, int64_t M, int64_t N, int64_t K, int g,
+                                     void* dX, bool bf16_out, float* slots, hipStream_t stream) {
+  const int64_t tm = (M + kDxTM - 1) / kDxTM, tk = (K + kDxTK - 1) / kDxTK;
+  const int64_t ntiles = tm * tk;
+  TilePlan t = dx_plan(M, N, K);
+  if (t.parts > 1 && !slots) {
+    if (bf16_out) return hipErrorInvalidValue;  // bfloat16 results are not added up in place
+    t = plan_atomic(ntiles, (N + kDxBN - 1) / kDxBN, current_cu_count());
+    if (t.rem && t.parts > 1) {  // these tiles are summed with atomics
+      const hipError_t e = launch_zero_tiles_f32(static_cast<float*>(dX), M, K, tk,
+                                                 ntiles - t.rem, t.rem, stream);
+      if (e != hipSuccess) return e;
+    }
+  }
+  const auto* cw = reinterpret_cast<const uint32_t*>(codes);
+  const dim3 grid((unsigned)t.grid), block(256);
+#define TM_DX_CASE(GG, BF_)                                                                     \
+  hipLaunchKernelGGL((tgemm_bwd_dx_kernel<GG, BF_>), grid, block, 0, stream, dY, cw,   \
+                     scales, M, N, K, dX, (uint32_t)tk, (uint32_t)t.full, (uint32_t)t.rem,      \
+                     (uint32_t)t.parts, t.per, slots)
+#define TM_DX_G(GG)            \
+  case GG:                     \
+    if (bf16_out)              \
+      TM_DX_CASE(GG, true);    \
+    else                       \
+      TM_DX_CASE(GG, false);   \
+    break;
+  switch (g) {
+    TM_DX_G(32)
+    TM_DX_G(64)
+    TM_DX_G(128)
+    TM_DX_G(256)
+    TM_DX_G(512)
+    default: return hipErrorInvalidValue;
+  }
+#undef TM_DX_G
+#undef TM_DX_CASE
+  const hipError_t e = hipGetLastError();
+  if (e != hipSuccess || t.parts == 1 || !slots) return e;
+  return launch_reduce_parts(slots, t.rem, t.parts, ntiles - t.rem, tk, M, K, dX, bf16_out,
+                             false, stream);
 }
 
 hipError_t launch_tgemm_bwd_dx(const uint16_t* dY, const uint8_t* codes, const float* scales,
                                int64_t M, int64_t N, int64_t K, int g, float* dX,
                                hipStream_t stream) {
-  const int64_t tm = (M + kDxTM - 1) / kDxTM, tk = (K + kDxTK - 1) / kDxTK;
-  const int64_t ntiles = tm * tk;
-  const int cus = current_cu_count();
-  const int64_t P = ntiles < cus ? ntiles : cus;
-  const int64_t rem = ntiles % P;
-  int64_t parts = rem ? P / rem : 1;
-  const int64_t nst = (N + kDxBN - 1) / kDxBN;
-  if (parts > nst) parts = nst;
-  if (rem) {  // the cut tiles are summed with atomics
-    const hipError_t e = launch_zero_tiles_f32(dX, M, K, tk, ntiles - rem, rem, stream);
-    if (e != hipSuccess) return e;
-  }
-  const auto* cw = reinterpret_cast<const uint32_t*>(codes);
-  const dim3 grid((unsigned)P), block(256);
-  const uint32_t t_k = (uint32_t)tk, nt = (uint32_t)ntiles, pa = (uint32_t)parts;
-  switch (g) {
-    case 32:  hipLaunchKernelGGL(tgemm_bwd_dx_kernel<32>, grid, block, 0, stream, dY, cw, scales, M, N, K, dX, t_k, nt, pa); break;
-    case 64:  hipLaunchKernelGGL(tgemm_bwd_dx_kernel<64>, grid, block, 0, stream, dY, cw, scales, M, N, K, dX, t_k, nt, pa); break;
-    case 128: hipLaunchKernelGGL(tgemm_bwd_dx_kernel<128>, grid, block, 0, stream, dY, cw, scales, M, N, K, dX, t_k, nt, pa); break;
-    case 256: hipLaunchKernelGGL(tgemm_bwd_dx_kernel<256>, grid, block, 0, stream, dY, cw, scales, M, N, K, dX, t_k, nt, pa); break;
-    case 512: hipLaunchKernelGGL(tgemm_bwd_dx_kernel<512>, grid, block, 0, stream, dY, cw, scales, M, N, K, dX, t_k, nt, pa); break;
-    default: return hipErrorInvalidValue;
-  }
-  return hipGetLastError();
+  return launch_tgemm_bwd_dx_parts(dY, codes, scales, M, N, K, g, dX, false, nullptr, stream);
 }
 
 }  // namespace tmk

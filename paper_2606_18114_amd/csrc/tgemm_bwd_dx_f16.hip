@@ -33,6 +33,8 @@
 // codes (the float16 values 2q) and one packed float16 multiply by the scale.
 #include "dx_common.hpp"
 #include "launchers.hpp"
+#include "tile_parts.hpp"
+#include "tile_store.hpp"
 
 namespace tmk {
 
@@ -89,15 +91,27 @@ __device__ __forceinline__ uint32_t bf16x2_to_f16x2(uint32_t w, int e) {
          ((uint32_t)__builtin_bit_cast(uint16_t, (_Float16)hi) << 16);
 }
 
+// two float32 values (as bits) rounded to bfloat16 (to nearest even), lo | hi << 16
+__device__ __forceinline__ uint32_t pack_bf16_bits(uint32_t lo, uint32_t hi) {
+  return (uint32_t)__builtin_bit_cast(uint16_t, (__bf16)__uint_as_float(lo)) |
+         ((uint32_t)__builtin_bit_cast(uint16_t, (__bf16)__uint_as_float(hi)) << 16);
+}
+
 // Prepass.  Waves 0 .. nparts-1 first take the largest magnitude in one
 // slice of the float32 scales (as unsigned bits) into parts[wave].  Then
 // every wave converts whole rows of dY: a row is held in registers (when it
 // has at most 64 * kPrepPieces pieces of 8 values, else read twice), its
 // largest magnitude gives e[m], and the row is written back as float16.
+// F32: dY arrives in float32; each value is rounded once to bfloat16 (to
+// nearest even), which is what the row maximum and the float16 copy are taken
+// from, and the bfloat16 row goes to dYb for the weight gradient.  HBM bound;
+// one pass moves 8 bytes per value where a cast and a bfloat16 prepass move
+// 10.
+template <bool F32>
 __global__ __launch_bounds__(256) void dx_prep_kernel(
-    const uint16_t* __restrict__ dY, const float* __restrict__ scales, int64_t M, int64_t N,
-    int64_t nsc, uint16_t* __restrict__ dY16, int32_t* __restrict__ rexp,
-    uint32_t* __restrict__ parts, int nparts) {
+    const void* __restrict__ dYv, const float* __restrict__ scales, int64_t M, int64_t N,
+    int64_t nsc, uint16_t* __restrict__ dY16, uint16_t* __restrict__ dYb,
+    int32_t* __restrict__ rexp, uint32_t* __restrict__ parts, int nparts) {
   const int lane = threadIdx.x & 63;
   const int64_t gw = (int64_t)blockIdx.x * 4 + (threadIdx.x >> 6);
   const int64_t nw = (int64_t)gridDim.x * 4;
@@ -110,11 +124,22 @@ __global__ __launch_bounds__(256) void dx_prep_kernel(
     v = wave_max_u32(v);
     if (lane == 0) parts[gw] = v;
   }
-  const int64_t npc = N / 8;  // 16-byte pieces per row (N % 8 == 0)
+  const int64_t npc = N / 8;  // pieces of 8 values per row (N % 8 == 0)
   const bool in_regs = npc <= 64 * kPrepPieces;
   for (int64_t m = gw; m < M; m += nw) {
-    const u32x4* src = reinterpret_cast<const u32x4*>(dY + m * N);
+    const u32x4* src = reinterpret_cast<const u32x4*>(dYv) + m * npc * (F32 ? 2 : 1);
     u32x4* dst = reinterpret_cast<u32x4*>(dY16 + m * N);
+    u32x4* dstb = reinterpret_cast<u32x4*>(dYb + m * N);
+    // piece p of the row as bfloat16
+    auto load = [&](int64_t p) {
+      if constexpr (F32) {
+        const u32x4 lo = src[2 * p], hi = src[2 * p + 1];
+        return u32x4{pack_bf16_bits(lo.x, lo.y), pack_bf16_bits(lo.z, lo.w),
+                     pack_bf16_bits(hi.x, hi.y), pack_bf16_bits(hi.z, hi.w)};
+      } else {
+        return src[p];
+      }
+    };
     u32x4 v[kPrepPieces];
     uint32_t mx = 0;
     auto fold = [&](const u32x4& p) {
@@ -125,11 +150,16 @@ __global__ __launch_bounds__(256) void dx_prep_kernel(
 #pragma unroll
       for (int i = 0; i < kPrepPieces; ++i) {
         const int64_t p = lane + 64 * i;
-        v[i] = p < npc ? src[p] : u32x4{0u, 0u, 0u, 0u};
+        v[i] = p < npc ? load(p) : u32x4{0u, 0u, 0u, 0u};
+        if (F32 && p < npc) dstb[p] = v[i];
         fold(v[i]);
       }
     } else {
-      for (int64_t p = lane; p < npc; p += 64) fold(src[p]);
+      for (int64_t p = lane; p < npc; p += 64) {
+        const u32x4 q = load(p);
+        if (F32) dstb[p] = q;
+        fold(q);
+      }
     }
     mx = wave_max_u32(mx);
     const int e = exp_to_2p14(mx >> 7, mx == 0 || mx >= 0x7F80u);
@@ -144,18 +174,21 @@ __global__ __launch_bounds__(256) void dx_prep_kernel(
         if (p < npc) dst[p] = conv(v[i]);
       }
     } else {
-      for (int64_t p = lane; p < npc; p += 64) dst[p] = conv(src[p]);
+      for (int64_t p = lane; p < npc; p += 64) dst[p] = conv(load(p));
     }
     if (lane == 0) rexp[m] = e;
   }
 }
 
-template <int G>
+// BF: dX in bfloat16 (each float32 sum rounded to nearest even once), else
+// float32; the bfloat16 form always has slots for its parts
+template <int G, bool BF>
 __global__ __launch_bounds__(256) void tgemm_bwd_dx_f16_kernel(
     const uint16_t* __restrict__ dY16, const int32_t* __restrict__ rexp,
     const uint32_t* __restrict__ sparts, int nparts, const uint32_t* __restrict__ codes,
     const float* __restrict__ scales, int64_t M, int64_t N, int64_t K,
-    float* __restrict__ dX, uint32_t tiles_k, uint32_t ntiles, uint32_t parts) {
+    void* __restrict__ dXv, uint32_t tiles_k, uint32_t full, uint32_t rem, uint32_t parts, int per,
+    float* __restrict__ slots) {
   __shared__ __attribute__((aligned(1024))) uint8_t lds[kHxLds];
   constexpr int kGpt = G < kHxTK ? kHxTK / G : 1;  // scale groups per tile row
 
@@ -169,8 +202,6 @@ __global__ __launch_bounds__(256) void tgemm_bwd_dx_f16_kernel(
   const int j16 = lane & 15;
   const uint32_t P = gridDim.x;
   const uint32_t bid = xcd_remap(blockIdx.x, P);
-  const uint32_t full = ntiles / P;
-  const uint32_t rem = ntiles % P;
   const int nst = (int)((N + kHxBN - 1) / kHxBN);
   const int64_t kw = K / 16;
   const int64_t ng = K / G;
@@ -216,14 +247,15 @@ __global__ __launch_bounds__(256) void tgemm_bwd_dx_f16_kernel(
       s_beg = 0;
       s_end = nst;
       whole = true;
-    } else if (item == full && rem != 0 && bid < rem * parts) {
-      tile = full * P + bid / parts;
-      const uint32_t part = bid % parts;
-      const int per = (nst + (int)parts - 1) / (int)parts;
+    } else if (item == full && bid < rem * parts) {
+      // part bid / rem of leftover tile bid % rem
+      // (the quotients are computed in vector registers: the loaders need
+      // them in scalar ones)
+      const uint32_t part = (uint32_t)__builtin_amdgcn_readfirstlane((int)(bid / rem));
+      tile = full * P + (bid - part * rem);
       s_beg = (int)part * per;
       s_end = s_beg + per < nst ? s_beg + per : nst;
-      whole = false;
-      if (s_beg >= s_end) break;
+      whole = parts == 1;
     } else {
       break;
     }
@@ -478,91 +510,121 @@ __global__ __launch_bounds__(256) void tgemm_bwd_dx_f16_kernel(
     asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
     __builtin_amdgcn_s_barrier();
 
-    // ---- write: lane holds column l32 of each block, rows 8 (i/4) + 4 h +
-    // i%4; dX = acc * 2^-(e[m] + t)
+    // ---- write: dX = acc * 2^-(e[m] + t)
     const int32_t* rxv = reinterpret_cast<const int32_t*>(lds + rx);
-    const int kleft = (int)(K - k0 - wk * 128 - l32);
-    const uint32_t lane_off = (uint32_t)(4 * h) * (uint32_t)K + (uint32_t)l32;
+    int ex[16];
+    auto prep = [&](int a) {
 #pragma unroll
-    for (int a = 0; a < 4; ++a) {
-      const int rowa = wm * 128 + 32 * a;
-      const int mleft = rows - rowa - 4 * h;
-      float* pa = dX + (m0 + rowa) * K + k0 + wk * 128;
-      int ex[16];
-#pragma unroll
-      for (int i = 0; i < 16; ++i) {
-        const int dm = 8 * (i / 4) + (i % 4);
-        const int r = rowa + 4 * h + dm;
-        ex[i] = -(rxv[r < kHxTM ? r : kHxTM - 1] + tsc);
-      }
-#pragma unroll
-      for (int b = 0; b < 4; ++b) {
-        if (kleft <= 32 * b) continue;
-#pragma unroll
-        for (int i = 0; i < 16; ++i) {
-          const int dm = 8 * (i / 4) + (i % 4);
-          if (dm < mleft) {
-            float* q = pa + 32 * b + (uint32_t)dm * (uint32_t)K + lane_off;
-            const float v = ldexpf(acc[a][b][i], ex[i]);
-            if (whole)
-              *q = v;
-            else
-              atomicAdd(q, v);
-          }
-        }
-        __builtin_amdgcn_sched_barrier(0);
-      }
-    }
+      for (int i = 0; i < 16; ++i)
+        ex[i] = -(rxv[wm * 128 + 32 * a + 4 * h + 8 * (i / 4) + (i % 4)] + tsc);
+    };
+    auto val = [&](int a, int b, int i) { return ldexpf(acc[a][b][i], ex[i]); };
+    using Out = std::conditional_t<BF, uint16_t, float>;
+    const int rows_left = rows - wm * 128;
+    const int64_t col0 = k0 + wk * 128;
+    const int cols_left = (int)(K - col0 < 256 ? K - col0 : 256);
+    Out* out = reinterpret_cast<Out*>(dXv) + (m0 + wm * 128) * K + col0;
+    if (whole)
+      tile_store(out, K, rows_left, cols_left, prep, val, [](Out* p, float v) {
+        if constexpr (BF)
+          *p = __builtin_bit_cast(uint16_t, (__bf16)v);
+        else
+          *p = v;
+      });
+    else if (BF || slots)
+      slot_store(slots + (int64_t)bid * kSlotFloats, rows_left, cols_left, prep, val);
+    else if constexpr (!BF)
+      tile_store(out, K, rows_left, cols_left, prep, val,
+                 [](float* p, float v) { atomicAdd(p, v); });
   }
   asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
 }
 
-hipError_t launch_tgemm_bwd_dx_f16(const uint16_t* dY, const uint8_t* codes, const float* scales,
-                                   int64_t M, int64_t N, int64_t K, int g, float* dX,
-                                   void* workspace, hipStream_t stream) {
+// Time of one group of ring stages (four, 128 weight rows) of a tile, of a
+// slot's write and read, and of the reduction's launch; see plan_parts
+constexpr double kHxUnitUs = 3.4, kHxSlotUs = 0.1, kHxLaunchUs = 5.0;
+
+static TilePlan hx_plan(int64_t M, int64_t N, int64_t K) {
+  const int64_t nt = ((M + kHxTM - 1) / kHxTM) * ((K + kHxTK - 1) / kHxTK);
+  return plan_parts(nt, (N + kHxBN - 1) / kHxBN, kHxRing, current_cu_count(), kHxUnitUs, kHxSlotUs,
+                    kHxLaunchUs);
+}
+
+int64_t bwd_dx_f16_slot_bytes(int64_t M, int64_t N, int64_t K) {
+  return hx_plan(M, N, K).slots() * kSlotBytes;
+}
+
+hipError_t launch_tgemm_bwd_dx_f16_parts(const void* dY, bool f32_in, uint16_t* dYb,
+                                         const uint8_t* codes, const float* scales, int64_t M,
+                                         int64_t N, int64_t K, int g, void* dX, bool bf16_out,
+                                         void* workspace, float* slots, hipStream_t stream) {
   auto up = [](int64_t v) { return (v + 255) / 256 * 256; };
   uint8_t* ws = static_cast<uint8_t*>(workspace);
   uint16_t* dY16 = reinterpret_cast<uint16_t*>(ws);
   int32_t* rexp = reinterpret_cast<int32_t*>(ws + up(M * N * 2));
   uint32_t* sparts = reinterpret_cast<uint32_t*>(ws + up(M * N * 2) + up(M * 4));
-  const int cus = current_cu_count();
-
   // prepass: up to 16 waves per CU, whole rows per wave
   {
-    const int64_t waves_cap = (int64_t)cus * 16;
+    const int64_t waves_cap = (int64_t)current_cu_count() * 16;
     int64_t waves = M < waves_cap ? M : waves_cap;
     if (waves < kScaleParts) waves = kScaleParts;  // the scale slices need kScaleParts
     const int64_t blocks = (waves + 3) / 4;
-    hipLaunchKernelGGL(dx_prep_kernel, dim3((unsigned)blocks), dim3(256), 0, stream, dY, scales,
-                       M, N, N * (K / g), dY16, rexp, sparts, kScaleParts);
+    if (f32_in)
+      hipLaunchKernelGGL(dx_prep_kernel<true>, dim3((unsigned)blocks), dim3(256), 0, stream, dY,
+                         scales, M, N, N * (K / g), dY16, dYb, rexp, sparts, kScaleParts);
+    else
+      hipLaunchKernelGGL(dx_prep_kernel<false>, dim3((unsigned)blocks), dim3(256), 0, stream, dY,
+                         scales, M, N, N * (K / g), dY16, nullptr, rexp, sparts, kScaleParts);
     const hipError_t e = hipGetLastError();
     if (e != hipSuccess) return e;
   }
 
   const int64_t tm = (M + kHxTM - 1) / kHxTM, tk = (K + kHxTK - 1) / kHxTK;
   const int64_t ntiles = tm * tk;
-  const int64_t P = ntiles < cus ? ntiles : cus;
-  const int64_t rem = ntiles % P;
-  int64_t parts = rem ? P / rem : 1;
-  const int64_t nst = (N + kHxBN - 1) / kHxBN;
-  if (parts > nst) parts = nst;
-  if (rem) {
-    const hipError_t e = launch_zero_tiles_f32(dX, M, K, tk, ntiles - rem, rem, stream);
-    if (e != hipSuccess) return e;
+  TilePlan t = hx_plan(M, N, K);
+  if (t.parts > 1 && !slots) {
+    if (bf16_out) return hipErrorInvalidValue;  // bfloat16 results are not added up in place
+    t = plan_atomic(ntiles, (N + kHxBN - 1) / kHxBN, current_cu_count());
+    if (t.rem && t.parts > 1) {  // these tiles are summed with atomics
+      const hipError_t e = launch_zero_tiles_f32(static_cast<float*>(dX), M, K, tk,
+                                                 ntiles - t.rem, t.rem, stream);
+      if (e != hipSuccess) return e;
+    }
   }
   const auto* cw = reinterpret_cast<const uint32_t*>(codes);
-  const dim3 grid((unsigned)P), block(256);
-  const uint32_t t_k = (uint32_t)tk, nt = (uint32_t)ntiles, pa = (uint32_t)parts;
-  const int np = kScaleParts;
+  const dim3 grid((unsigned)t.grid), block(256);
+#define TM_DX_CASE(GG, BF_)                                                                     \
+  hipLaunchKernelGGL((tgemm_bwd_dx_f16_kernel<GG, BF_>), grid, block, 0, stream, dY16, rexp, sparts, kScaleParts, cw,   \
+                     scales, M, N, K, dX, (uint32_t)tk, (uint32_t)t.full, (uint32_t)t.rem,      \
+                     (uint32_t)t.parts, t.per, slots)
+#define TM_DX_G(GG)            \
+  case GG:                     \
+    if (bf16_out)              \
+      TM_DX_CASE(GG, true);    \
+    else                       \
+      TM_DX_CASE(GG, false);   \
+    break;
   switch (g) {
-    case 32:  hipLaunchKernelGGL(tgemm_bwd_dx_f16_kernel<32>, grid, block, 0, stream, dY16, rexp, sparts, np, cw, scales, M, N, K, dX, t_k, nt, pa); break;
-    case 64:  hipLaunchKernelGGL(tgemm_bwd_dx_f16_kernel<64>, grid, block, 0, stream, dY16, rexp, sparts, np, cw, scales, M, N, K, dX, t_k, nt, pa); break;
-    case 128: hipLaunchKernelGGL(tgemm_bwd_dx_f16_kernel<128>, grid, block, 0, stream, dY16, rexp, sparts, np, cw, scales, M, N, K, dX, t_k, nt, pa); break;
-    case 256: hipLaunchKernelGGL(tgemm_bwd_dx_f16_kernel<256>, grid, block, 0, stream, dY16, rexp, sparts, np, cw, scales, M, N, K, dX, t_k, nt, pa); break;
-    case 512: hipLaunchKernelGGL(tgemm_bwd_dx_f16_kernel<512>, grid, block, 0, stream, dY16, rexp, sparts, np, cw, scales, M, N, K, dX, t_k, nt, pa); break;
+    TM_DX_G(32)
+    TM_DX_G(64)
+    TM_DX_G(128)
+    TM_DX_G(256)
+    TM_DX_G(512)
     default: return hipErrorInvalidValue;
   }
-  return hipGetLastError();
+#undef TM_DX_G
+#undef TM_DX_CASE
+  const hipError_t e = hipGetLastError();
+  if (e != hipSuccess || t.parts == 1 || !slots) return e;
+  return launch_reduce_parts(slots, t.rem, t.parts, ntiles - t.rem, tk, M, K, dX, bf16_out,
+                             false, stream);
+}
+
+hipError_t launch_tgemm_bwd_dx_f16(const uint16_t* dY, const uint8_t* codes, const float* scales,
+                                   int64_t M, int64_t N, int64_t K, int g, float* dX,
+                                   void* workspace, hipStream_t stream) {
+  return launch_tgemm_bwd_dx_f16_parts(dY, false, nullptr, codes, scales, M, N, K, g, dX, false,
+                                       workspace, nullptr, stream);
 }
 
 }  // namespace tmk

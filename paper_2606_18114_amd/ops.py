@@ -81,6 +81,15 @@ SIGNATURES = {
     "tm_mamba2_decode_workspace": (ctypes.c_int64, [_I32, _I32, _I32]),
 }
 
+# the calls of include/tmamba_parts.h
+SIGNATURES_PARTS = {
+    "tm_tgemm_bwd_dx_slots": (ctypes.c_int64, [_I64, _I64, _I64, _I32]),
+    "tm_tgemm_bwd_dw_slots": (ctypes.c_int64, [_I64, _I64, _I64]),
+    "tm_tgemm_bwd_dx_parts": (ctypes.c_int, [_P, _I32, _P, _P, _P, _I64, _I64, _I64, _I32, _I32,
+                                             _P, _I32, _P, _I64, _P, _I64, _P]),
+    "tm_tgemm_bwd_dw_parts": (ctypes.c_int, [_P, _P, _I64, _I64, _I64, _P, _I32, _P, _I64, _P]),
+}
+
 
 class TernaryError(RuntimeError):
     def __init__(self, fn: str, status: int):
@@ -102,7 +111,7 @@ def lib() -> ctypes.CDLL:
                 f"{_LIB_PATH} is missing: build it with `python -m paper_2606_18114_amd.build` "
                 "(or __graft_entry__.build()); there is no fallback implementation")
         L = ctypes.CDLL(_LIB_PATH)
-        for name, (res, args) in SIGNATURES.items():
+        for name, (res, args) in (*SIGNATURES.items(), *SIGNATURES_PARTS.items()):
             f = getattr(L, name)
             f.restype = res
             f.argtypes = args
@@ -364,25 +373,80 @@ def tgemm_bwd_dx(dY: torch.Tensor, codes: torch.Tensor, scales: torch.Tensor, g:
         dX = torch.empty((M, K), dtype=torch.float32, device=dY.device)
     _need(dX, "dX", _F32, 2)
     _shape(dX, "dX", (M, K), dY.device)
-    if precision == "exact":
-        st = lib().tm_tgemm_bwd_dx(_ptr(dY), _ptr(codes), _ptr(scales), M, N, K, g, _ptr(dX),
-                                   _stream())
-        _check("tm_tgemm_bwd_dx", st)
-        return dX
-    if precision != "f16":
+    if precision not in ("exact", "f16"):
         raise ValueError(f"precision must be 'f16' or 'exact' (got {precision!r})")
-    need = dx_f16_workspace_bytes(M, N)
-    if workspace is None:
-        workspace = torch.empty(need, dtype=torch.uint8, device=dY.device)
-    _need(workspace, "workspace", _U8, 1)
-    if workspace.numel() < need:
-        raise ValueError(f"workspace has {workspace.numel()} bytes, {need} needed")
-    if workspace.device != dY.device:
-        raise ValueError(f"workspace is on {workspace.device}, the operands on {dY.device}")
-    st = lib().tm_tgemm_bwd_dx_f16(_ptr(dY), _ptr(codes), _ptr(scales), M, N, K, g, _ptr(dX),
-                                   _ptr(workspace), workspace.numel(), _stream())
-    _check("tm_tgemm_bwd_dx_f16", st)
+    _bwd_dx(dY, None, codes, scales, M, N, K, g, precision == "exact", dX, workspace)
     return dX
+
+
+def _bwd_dx(dY, dY16, codes, scales, M, N, K, g, exact, dX, workspace) -> None:
+    """The dX call on checked operands: dY bfloat16, or float32 with dY16 the
+    bfloat16 copy to write; dX float32 or bfloat16."""
+    wp, wb = None, 0
+    if not exact:
+        need = dx_f16_workspace_bytes(M, N)
+        if workspace is None:
+            workspace = torch.empty(need, dtype=torch.uint8, device=dX.device)
+        _need(workspace, "workspace", _U8, 1)
+        if workspace.numel() < need:
+            raise ValueError(f"workspace has {workspace.numel()} bytes, {need} needed")
+        if workspace.device != dX.device:
+            raise ValueError(f"workspace is on {workspace.device}, the operands on {dX.device}")
+        wp, wb = _ptr(workspace), workspace.numel()
+    out16 = dX.dtype == torch.bfloat16
+    slots = _slots(lib().tm_tgemm_bwd_dx_slots(M, N, K, int(exact)), dX.device, required=out16)
+    st = lib().tm_tgemm_bwd_dx_parts(_ptr(dY), int(dY16 is not None), _ptr(dY16), _ptr(codes),
+                                     _ptr(scales), M, N, K, g, int(exact), _ptr(dX), int(out16),
+                                     wp, wb, _ptr(slots), 0 if slots is None else slots.numel(),
+                                     _stream())
+    _check("tm_tgemm_bwd_dx" if exact else "tm_tgemm_bwd_dx_f16", st)
+
+
+def _slots(nbytes: int, device: torch.device, required: bool = False) -> Optional[torch.Tensor]:
+    """Scratch of one call for the parts of cut tiles: None where no tile is
+    cut, and, unless the call cannot do without, where the memory for it is
+    not there (the parts then add up in the output by atomics)."""
+    if nbytes <= 0:
+        return None
+    try:
+        return torch.empty(nbytes, dtype=torch.uint8, device=device)
+    except torch.OutOfMemoryError:
+        if required:
+            raise
+        return None
+
+
+def layer_input_grad(gy: torch.Tensor, codes: torch.Tensor, scales: torch.Tensor, g: int = 128,
+                     *, precision: str = "f16"):
+    """A layer's input gradient from the gradient gy [M, N] of its output,
+    bfloat16 or float32: (dX bfloat16 [M, K], the float32 sums rounded once,
+    and gy rounded to bfloat16 [M, N], gy itself if it is bfloat16).  The
+    same values as casting gy to bfloat16, ``tgemm_bwd_dx`` and casting its
+    result, without the casts' passes over memory."""
+    _need(gy, "gy", (torch.bfloat16, torch.float32), 2)
+    _need(codes, "codes", _U8, 2)
+    _need(scales, "scales", _F32, 2)
+    M, N = gy.shape
+    K = codes.shape[1] * 4
+    _shape(codes, "codes", (N, K // 4), gy.device)
+    _shape(scales, "scales", (N, _groups(K, g)), gy.device)
+    if precision not in ("exact", "f16"):
+        raise ValueError(f"precision must be 'f16' or 'exact' (got {precision!r})")
+    exact = precision == "exact"
+    gy16 = None
+    if gy.dtype == torch.float32:
+        if exact or gy.data_ptr() % 16:  # the fused rounding reads 16 bytes at a time
+            gy = gy.to(torch.bfloat16)
+        else:
+            gy16 = torch.empty((M, N), dtype=torch.bfloat16, device=gy.device)
+    try:
+        dX = torch.empty((M, K), dtype=torch.bfloat16, device=gy.device)
+        _bwd_dx(gy, gy16, codes, scales, M, N, K, g, exact, dX, None)
+    except torch.OutOfMemoryError:
+        # no room for the parts' scratch: add up in float32, then round
+        dy = gy if gy16 is None else gy.to(torch.bfloat16)
+        return tgemm_bwd_dx(dy, codes, scales, g, precision=precision).to(torch.bfloat16), dy
+    return dX, gy if gy16 is None else gy16
 
 
 def dx_f16_workspace_bytes(M: int, N: int) -> int:
@@ -407,8 +471,10 @@ def tgemm_bwd_dw_ste(dY: torch.Tensor, X: torch.Tensor, dW: Optional[torch.Tenso
         dW = torch.empty((N, K), dtype=torch.float32, device=dY.device)
     _need(dW, "dW", _F32, 2)
     _shape(dW, "dW", (N, K), dY.device)
-    st = lib().tm_tgemm_bwd_dw_ste(_ptr(dY), _ptr(X), M, N, K, _ptr(dW), int(accumulate),
-                                   _stream())
+    slots = _slots(lib().tm_tgemm_bwd_dw_slots(M, N, K), dY.device)
+    st = lib().tm_tgemm_bwd_dw_parts(_ptr(dY), _ptr(X), M, N, K, _ptr(dW), int(accumulate),
+                                     _ptr(slots), 0 if slots is None else slots.numel(),
+                                     _stream())
     _check("tm_tgemm_bwd_dw_ste", st)
     return dW
 

@@ -99,13 +99,18 @@ class TernaryLinearFn(torch.autograd.Function):
         x2, codes, mag, w = ctx.saved_tensors
         N = codes.shape[0]
         dy = gy.reshape(-1, N)
-        if dy.dtype != torch.bfloat16:
-            dy = dy.to(torch.bfloat16)
-        dy = dy.contiguous()
         dx = dw = dscale = None
         if ctx.needs_input_grad[0]:
-            dx = ops.tgemm_bwd_dx(dy, codes, mag, ctx.g, precision=ctx.dx_precision)
+            # rounds a contiguous float32 gradient to bfloat16 on the way, and dX once
+            if not (dy.dtype == torch.float32 and dy.is_contiguous()):
+                dy = dy.to(torch.bfloat16)
+            dx, dy = ops.layer_input_grad(dy.contiguous(), codes, mag, ctx.g,
+                                          precision=ctx.dx_precision)
             dx = dx.to(ctx.x_dtype).reshape(*ctx.lead, x2.shape[1])
+        else:
+            if dy.dtype != torch.bfloat16:
+                dy = dy.to(torch.bfloat16)
+            dy = dy.contiguous()
         want_scale = ctx.learned and ctx.needs_input_grad[2]
         if ctx.needs_input_grad[1] or want_scale:
             dw_hat = ops.tgemm_bwd_dw_ste(dy, x2)   # gradient w.r.t. the dequantized weights

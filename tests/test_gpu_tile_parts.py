@@ -1,0 +1,86 @@
+"""The training products where output tiles are cut along the contraction and
+their parts meet in a scratch buffer: dX (both forms, float32 and bfloat16,
+from a bfloat16 or a float32 gradient) and dW (stored and accumulated), on
+shapes with fewer 256 x 256 tiles than compute units, ragged edges, one part,
+the most parts, and a remainder after whole rounds; against float64."""
+
+import pytest
+
+torch = pytest.importorskip("torch")
+
+from paper_2606_18114_amd import ops  # noqa: E402
+
+pytestmark = pytest.mark.gpu
+
+# (M, N, K, g): tokens, out features, in features
+SHAPES = [(1, 256, 64, 32), (16, 256, 512, 128), (300, 1032, 768, 64), (257, 4104, 320, 64),
+          (1000, 3352, 768, 256), (2050, 2056, 512, 512), (129, 8512, 2048, 128),
+          (4352, 4096, 1024, 128)]
+
+
+@pytest.fixture(autouse=True)
+def _gpu():
+    if not torch.cuda.is_available():
+        pytest.skip("no GPU")
+
+
+def _operands(M, N, K, g, seed=0):
+    gen = torch.Generator(device="cuda").manual_seed(seed)
+    w = torch.randn((N, K), generator=gen, device="cuda") * 0.02
+    x = torch.randn((M, K), generator=gen, device="cuda").to(torch.bfloat16)
+    dy = torch.randn((M, N), generator=gen, device="cuda") * 0.01
+    codes, s, _, _ = ops.ternarize_pack(w, g, 1e-5)
+    tau = (s + 1e-5).repeat_interleave(g, dim=1)
+    what = (torch.sign(w) * (w.abs() > 0.5 * tau)).double() * s.double().repeat_interleave(g, 1)
+    return x, dy, codes, s, what
+
+
+def _rel(a, ref):
+    return float((a.double() - ref).norm() / ref.norm())
+
+
+@pytest.mark.parametrize("M,N,K,g", SHAPES)
+@pytest.mark.parametrize("precision", ["f16", "exact"])
+def test_input_grad(M, N, K, g, precision):
+    print(f"[parts] dX {precision} M={M} N={N} K={K} g={g}", flush=True)
+    _, dy, codes, s, what = _operands(M, N, K, g)
+    dyb = dy.to(torch.bfloat16)
+    ref = dyb.double() @ what
+    dX = ops.tgemm_bwd_dx(dyb, codes, s, g, precision=precision)
+    # float16 keeps 11 bits of a scale (2^-12 rms of a rounding), the two-pass
+    # form 16 bits; the float32 sums add less
+    assert _rel(dX, ref) <= (2.0 ** -11 if precision == "f16" else 2.0 ** -15)
+    assert torch.equal(dX, ops.tgemm_bwd_dx(dyb, codes, s, g, precision=precision))
+    for gy in (dyb, dy):  # a bfloat16 result is the float32 one rounded once
+        dX16, gy16 = ops.layer_input_grad(gy, codes, s, g, precision=precision)
+        assert dX16.dtype == torch.bfloat16 and torch.equal(dX16, dX.to(torch.bfloat16))
+        assert torch.equal(gy16, dyb)
+
+
+@pytest.mark.parametrize("M,N,K,g", SHAPES)
+def test_weight_grad(M, N, K, g):
+    print(f"[parts] dW M={M} N={N} K={K}", flush=True)
+    x, dy, _, _, _ = _operands(M, N, K, g)
+    dyb = dy.to(torch.bfloat16)
+    ref = dyb.double().t() @ x.double()
+    dW = ops.tgemm_bwd_dw_ste(dyb, x)
+    # float32 sums of exact products: random rounding of M terms
+    tol = 2.0 ** -23 * max(M, 16) ** 0.5
+    assert _rel(dW, ref) <= tol
+    assert torch.equal(dW, ops.tgemm_bwd_dw_ste(dyb, x))
+    acc = torch.ones_like(dW)
+    ops.tgemm_bwd_dw_ste(dyb, x, acc, accumulate=True)
+    assert _rel(acc, ref + 1) <= tol + 2.0 ** -24
+
+
+def test_float32_gradient_rounding():
+    """Ties, infinities, NaN and subnormals round as torch's cast does."""
+    _, dy, codes, s, _ = _operands(16, 256, 512, 128)
+    bits = torch.arange(16 * 256, device="cuda", dtype=torch.int64) * 1048583 % (1 << 32)
+    dy = bits.to(torch.int32).view(torch.float32).reshape(16, 256).contiguous()
+    dy[0, :4] = torch.tensor([float("inf"), float("-inf"), float("nan"), 1e-40], device="cuda")
+    _, got = ops.layer_input_grad(dy, codes, s, 128)
+    ref = dy.to(torch.bfloat16)
+    nan = ref.isnan()
+    assert torch.equal(got.isnan(), nan)
+    assert torch.equal(got[~nan].view(torch.int16), ref[~nan].view(torch.int16))
