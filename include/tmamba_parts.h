@@ -19,8 +19,19 @@
 extern "C" {
 #endif
 
+int64_t tm_tgemm_fwd_slots(int64_t M, int64_t N, int64_t K, int32_t g);
 int64_t tm_tgemm_bwd_dx_slots(int64_t M, int64_t N, int64_t K, int32_t exact);
 int64_t tm_tgemm_bwd_dw_slots(int64_t M, int64_t N, int64_t K);
+
+/*
+ * Y = X . What^T in float32 (y_bf16 = 0) or rounded once to bfloat16
+ * (y_bf16 = 1), on the tile shape and cut that suit the sizes.  workspace:
+ * NULL, or that of tm_tgemm_fwd_ws (float32 only).
+ */
+tm_status tm_tgemm_fwd_parts(const uint16_t* X, const uint8_t* codes, const float* scales,
+                             int64_t M, int64_t N, int64_t K, int32_t g, void* Y, int32_t y_bf16,
+                             void* workspace, int64_t workspace_bytes, float* slots,
+                             int64_t slots_bytes, tm_stream stream);
 
 /*
  * dX[M, K] = dY . What in float32 (dx_bf16 = 0) or rounded once to bfloat16

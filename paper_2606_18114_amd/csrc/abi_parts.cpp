@@ -39,6 +39,28 @@ int64_t tm_tgemm_bwd_dw_slots(int64_t M, int64_t N, int64_t K) {
   return tmk::bwd_dw_slot_bytes(M, N, K);
 }
 
+int64_t tm_tgemm_fwd_slots(int64_t M, int64_t N, int64_t K, int32_t g) {
+  if (!sizes_ok(M, N, K) || shape_kg(K, g) != TM_OK) return -1;
+  return tmk::fwd_slot_bytes(M, N, K, g);
+}
+
+tm_status tm_tgemm_fwd_parts(const uint16_t* X, const uint8_t* codes, const float* scales,
+                             int64_t M, int64_t N, int64_t K, int32_t g, void* Y, int32_t y_bf16,
+                             void* workspace, int64_t workspace_bytes, float* slots,
+                             int64_t slots_bytes, tm_stream stream) {
+  if ((y_bf16 & ~1) || (y_bf16 && workspace)) return TM_EINVAL;
+  const int es = y_bf16 ? 2 : 4;
+  if (tm_status st = fwd_checked(X, codes, scales, M, N, K, g, Y, es, workspace, workspace_bytes))
+    return st;
+  const int64_t need = tm_tgemm_fwd_slots(M, N, K, g);
+  const Span ops[5] = {span(X, M * K * 2), span(codes, N * (K / 4)), span(scales, N * (K / g) * 4),
+                       span(Y, M * N * es), span(workspace, workspace ? kFwdTicketBytes : 0)};
+  if (tm_status st = slots_checked(slots, slots_bytes, need, ops, 5)) return st;
+  return hip_status(tmk::launch_tgemm_fwd_parts(X, codes, scales, M, N, K, g, Y, y_bf16 != 0,
+                                                static_cast<uint32_t*>(workspace), slots,
+                                                slots != nullptr || need == 0, to_hip(stream)));
+}
+
 tm_status tm_tgemm_bwd_dx_parts(const void* dY, int32_t dy_f32, uint16_t* dY_bf16,
                                 const uint8_t* codes, const float* scales, int64_t M, int64_t N,
                                 int64_t K, int32_t g, int32_t exact, void* dX, int32_t dx_bf16,

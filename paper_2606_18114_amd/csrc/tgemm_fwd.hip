@@ -50,10 +50,11 @@
 
 #include "common.hpp"
 #include "launchers.hpp"
+#include "tile_parts.hpp"
 
 namespace tmk {
 
-constexpr int kFwdBM = 256, kFwdBN = 256, kFwdBK = 64;
+constexpr int kFwdBK = 64;
 constexpr int kFwdXRing = 3;
 // polls of a cut tile's flag before the second part gives up waiting (the
 // first part is already storing when the second starts to wait; this bound
@@ -61,16 +62,23 @@ constexpr int kFwdXRing = 3;
 constexpr uint32_t kFwdSpinLimit = 1u << 20;
 // fewest cut tiles for which the two parts meet through the tickets
 constexpr int64_t kFwdMinTicketTiles = 16;
-constexpr int kFwdXStage = kFwdBM * kFwdBK * 2;  // 32 KiB of X per stage
 
-// SS: X stages per code stage (4 when K % 256 == 0, else 1)
-template <int G, int SS>
+// SS: X stages per code stage (4 when K % 256 == 0, else 1).
+// MA, NW: 32-row blocks per wave and waves per workgroup (2 rows of NW / 2
+// waves of 32 MA x 64 outputs): (4, 8) 256 x 256 tiles, (2, 4) 128 x 128,
+// (1, 4) 64 x 128.  The three have the same loads per wave and stage, but
+// for X in the last.
+template <int G, int SS, int MA, int NW>
 struct FwdCfg {
+  static constexpr int kBM = 64 * MA, kBN = 32 * NW;
+  static constexpr int kXStage = kBM * kFwdBK * 2;   // X bytes per stage
+  static constexpr int kNx = kXStage / 1024 / NW;    // X loads per wave per stage
+  static constexpr int kSlotFloats = kBM * kBN;
   static constexpr int kNs = SS == 1 ? 2 : (256 / G > 2 ? 256 / G : 2);  // scales per row
   static constexpr int kCRing = SS == 1 ? 3 : 2;
-  static constexpr int kCStage = kFwdBN * 16 * SS;  // code bytes per code stage
-  static constexpr int kSStage = kFwdBN * kNs * 4;  // scale bytes per code stage
-  static constexpr int kCBase = kFwdXRing * kFwdXStage;
+  static constexpr int kCStage = kBN * 16 * SS;  // code bytes per code stage
+  static constexpr int kSStage = kBN * kNs * 4;  // scale bytes per code stage
+  static constexpr int kCBase = kFwdXRing * kXStage;
   static constexpr int kSBase = kCBase + kCRing * kCStage;
   static constexpr int kLds = kSBase + kCRing * kSStage;
   static constexpr int kScaleDma = SS == 1 ? 1 : kNs / 2;  // per wave per code stage
@@ -122,20 +130,21 @@ __device__ __forceinline__ void static_for(F&& f) {
 }
 
 // BF: Y in bfloat16 (each float32 result rounded to nearest even once),
-// else float32.  The bfloat16 form never cuts tiles (parts == 1).
-template <int G, int SS, bool BF>
-__global__ __launch_bounds__(512) void tgemm_fwd_kernel(
+// else float32.  The bfloat16 form cuts tiles only with slots.
+template <int G, int SS, bool BF, int MA, int NW>
+__global__ __launch_bounds__(64 * NW, 2) void tgemm_fwd_kernel(
     const uint16_t* __restrict__ X, const uint8_t* __restrict__ codes,
     const float* __restrict__ scales, int64_t M, int64_t N, int64_t K,
     void* __restrict__ Yv, uint32_t tiles_n, uint32_t full_rounds, uint32_t extra_units,
-    uint32_t parts, uint32_t* __restrict__ tickets) {
-  using C = FwdCfg<G, SS>;
+    uint32_t parts, uint32_t* __restrict__ tickets, float* __restrict__ slots) {
+  using C = FwdCfg<G, SS, MA, NW>;
+  constexpr int kFwdXStage = C::kXStage, kFwdBM = C::kBM, kFwdBN = C::kBN;
   __shared__ __attribute__((aligned(1024))) uint8_t lds[C::kLds];
   __shared__ uint32_t tk_word;  // arrival order of this workgroup at its cut tile
 
   const int lane = threadIdx.x & 63;
   const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-  const int wm = wave >> 2, wn = wave & 3;
+  const int wm = wave / (NW / 2), wn = wave % (NW / 2);
   const uint32_t h = (uint32_t)(lane >> 5);  // k half of the MFMA operands
   const int l32 = lane & 31;
   const int nst = (int)(K / kFwdBK);
@@ -145,6 +154,9 @@ __global__ __launch_bounds__(512) void tgemm_fwd_kernel(
   const uint32_t nblk = gridDim.x;
   const uint32_t lds0 = (uint32_t)(uintptr_t)lds;
   // in-tile row offsets of the output fit 32 bits (131 rows of N floats)
+  // 128-byte rows of a block are whole cache lines: streamed past the caches.
+  // Otherwise the caches join the two blocks that share a line.
+  const bool whole_lines = N % 32 == 0;
   const bool small_pitch = N < (int64_t(1) << 22);
 
   // Work list of this workgroup: full_rounds whole tiles (tile r * nblk + bid
@@ -159,11 +171,20 @@ __global__ __launch_bounds__(512) void tgemm_fwd_kernel(
   // sums into Y with coherent stores and then raises word 2t + 1; the second
   // waits for that word and adds its sums with atomics.  Two addends give the
   // same bits in either order, and only half the atomics.
+  // With slots every part of a cut tile (part p of the j-th is run by
+  // workgroup p * (cut tiles) + j) writes its sums to its slot, and a
+  // reduction adds them (tile_parts.hpp).
   const uint32_t F = full_rounds;
   const bool has_x = bid < extra_units;
   const uint32_t nu = F + (has_x ? 1u : 0u);
   if (nu == 0) return;  // no work: before any load or barrier
-  const uint32_t xp = has_x ? bid % parts : 0u;
+  const uint32_t ncut = slots ? extra_units / parts : 1u;  // (slots: cut tiles)
+  // (the quotients are computed in vector registers: the loaders need them
+  // in scalar ones)
+  const uint32_t xq = (uint32_t)__builtin_amdgcn_readfirstlane(
+      (int)(slots ? bid / ncut : bid / parts));
+  const uint32_t xp = has_x ? (slots ? xq : bid - xq * parts) : 0u;
+  const uint32_t xtile = F * nblk + (slots ? bid - xq * ncut : xq);
   const bool x_first = has_x && parts > 1 && (xp & 1u);
   const int trips = nst / C::kUnroll;
   // unit u (units past the end repeat the last one: their loads are never
@@ -173,7 +194,7 @@ __global__ __launch_bounds__(512) void tgemm_fwd_kernel(
     u = u < nu ? u : nu - 1;
     const bool extra = has_x && (x_first ? u == 0 : u == F);
     if (extra) {
-      tile = F * nblk + bid / parts;
+      tile = xtile;
       s0 = (int)(xp * (uint32_t)trips / parts) * C::kUnroll;
       s1 = (int)((xp + 1) * (uint32_t)trips / parts) * C::kUnroll;
       part = parts > 1;
@@ -194,18 +215,18 @@ __global__ __launch_bounds__(512) void tgemm_fwd_kernel(
   uint32_t xu = 0;
   int xst = 0, xend = 0, xslot = 0;
   const uint8_t* xt = nullptr;
-  uint32_t xoff[4];
+  uint32_t xoff[C::kNx];
   auto set_xunit = [&](uint32_t u) {
     uint32_t tile;
     bool part;
     int64_t m0, n0;
     unit_of(u, tile, xst, xend, part);
     tile_rows(tile, m0, n0);
-    const int mlast = (int)(M - 1 - m0 < 255 ? M - 1 - m0 : 255);
+    const int mlast = (int)(M - 1 - m0 < kFwdBM - 1 ? M - 1 - m0 : kFwdBM - 1);
     xt = reinterpret_cast<const uint8_t*>(X + m0 * K);
 #pragma unroll
-    for (int i = 0; i < 4; ++i) {  // load I = rows 8I .. 8I+7
-      const int r = 8 * (wave * 4 + i) + (lane >> 3);
+    for (int i = 0; i < C::kNx; ++i) {  // load I = rows 8I .. 8I+7
+      const int r = 8 * (wave * C::kNx + i) + (lane >> 3);
       const int lp = (lane & 7) ^ fwd_xswz(r);  // logical piece this lane fetches
       xoff[i] = (uint32_t)(r < mlast ? r : mlast) * (uint32_t)K * 2u + 16u * lp;
     }
@@ -215,8 +236,8 @@ __global__ __launch_bounds__(512) void tgemm_fwd_kernel(
   auto dma_x = [&](auto may_wrap) {
     const uint8_t* base = xt + (int64_t)xst * kFwdBK * 2;
 #pragma unroll
-    for (int i = 0; i < 4; ++i)
-      dma_x16(base, xoff[i], lds0 + xslot * kFwdXStage + 1024 * (wave * 4 + i));
+    for (int i = 0; i < C::kNx; ++i)
+      dma_x16(base, xoff[i], lds0 + xslot * kFwdXStage + 1024 * (wave * C::kNx + i));
     xslot = xslot == kFwdXRing - 1 ? 0 : xslot + 1;
     ++xst;
     if constexpr (decltype(may_wrap)::value) {
@@ -235,7 +256,7 @@ __global__ __launch_bounds__(512) void tgemm_fwd_kernel(
     int64_t m0, n0;
     unit_of(u, tile, cst, cend, part);
     tile_rows(tile, m0, n0);
-    const int nlast = (int)(N - 1 - n0 < 255 ? N - 1 - n0 : 255);
+    const int nlast = (int)(N - 1 - n0 < kFwdBN - 1 ? N - 1 - n0 : kFwdBN - 1);
     ct = codes + n0 * kb;
     stl = reinterpret_cast<const uint8_t*>(scales + n0 * ng);
 #pragma unroll
@@ -290,9 +311,9 @@ __global__ __launch_bounds__(512) void tgemm_fwd_kernel(
   dma_x(wraps);
   if constexpr (SS == 1) {
     dma_c(wraps);
-    fwd_stage_barrier<4 + C::kNc>();
+    fwd_stage_barrier<C::kNx + C::kNc>();
   } else {
-    fwd_stage_barrier<4>();
+    fwd_stage_barrier<C::kNx>();
   }
 
   const int xsw = fwd_xswz(l32);  // == fwd_xswz(m) for every X row m this lane reads
@@ -307,9 +328,9 @@ __global__ __launch_bounds__(512) void tgemm_fwd_kernel(
     unit_of(u, tile, s0, s1, part);
     tile_rows(tile, m0, n0);
 
-    f32x16 acc[4][2];
+    f32x16 acc[MA][2];
 #pragma unroll
-    for (int a = 0; a < 4; ++a)
+    for (int a = 0; a < MA; ++a)
 #pragma unroll
       for (int b = 0; b < 2; ++b)
 #pragma unroll
@@ -352,13 +373,13 @@ __global__ __launch_bounds__(512) void tgemm_fwd_kernel(
       }
       auto read_a = [&](int t, bf16x8* ao) {
 #pragma unroll
-        for (int a = 0; a < 4; ++a) {
-          const int m = wm * 128 + a * 32 + l32;
+        for (int a = 0; a < MA; ++a) {
+          const int m = wm * 32 * MA + a * 32 + l32;
           ao[a] = as_bf16x8(*reinterpret_cast<const u32x4*>(
               xb + 128 * m + 16 * ((2 * t + (int)h) ^ xsw)));
         }
       };
-      bf16x8 acur[4];
+      bf16x8 acur[MA];
       read_a(0, acur);
 #pragma unroll
       for (int t = 0; t < 4; ++t) {
@@ -377,10 +398,10 @@ __global__ __launch_bounds__(512) void tgemm_fwd_kernel(
         }
         bf16x8 bop[2];
         decode_half_pair_rt(u32x2{cw[0][t] & msk[0], cw[1][t] & msk[1]}, hs, bop[0], bop[1]);
-        bf16x8 anext[4];
+        bf16x8 anext[MA];
         if (t < 3) read_a(t + 1, anext);
 #pragma unroll
-        for (int a = 0; a < 4; ++a) {
+        for (int a = 0; a < MA; ++a) {
 #pragma unroll
           for (int b = 0; b < 2; ++b) {
             if (start) acc[a][b] *= r[b];
@@ -389,7 +410,7 @@ __global__ __launch_bounds__(512) void tgemm_fwd_kernel(
         }
         if (t < 3) {
 #pragma unroll
-          for (int a = 0; a < 4; ++a) acur[a] = anext[a];
+          for (int a = 0; a < MA; ++a) acur[a] = anext[a];
         }
       }
     };
@@ -410,9 +431,9 @@ __global__ __launch_bounds__(512) void tgemm_fwd_kernel(
           dma_c(std::integral_constant<bool, (i + kCAhead) % C::kUnroll == 0>{});
         stage(std::integral_constant<int, P>{}, std::integral_constant<bool, kStart>{});
         if constexpr (SS == 1 || P < 2)
-          fwd_stage_barrier<4 + C::kNc>();
+          fwd_stage_barrier<C::kNx + C::kNc>();
         else
-          fwd_stage_barrier<4>();
+          fwd_stage_barrier<C::kNx>();
         xs = xs == kFwdXRing - 1 ? 0 : xs + 1;
         if constexpr (SS == 1)
           cs = xs;
@@ -427,10 +448,10 @@ __global__ __launch_bounds__(512) void tgemm_fwd_kernel(
     // the row test (rows past M only occur in the last row of tiles).  Parts
     // of a tile add their partial sums with float32 atomics.
     {
-      const int64_t mrow = m0 + wm * 128;
+      const int64_t mrow = m0 + wm * 32 * MA;
       constexpr int ES = BF ? 2 : 4;  // bytes per output element
       // two-part cut tile with tickets: which part arrives first
-      const bool tk = !BF && part && tickets != nullptr;
+      const bool tk = !BF && NW == 8 && part && tickets != nullptr;
       const uint32_t tkt = 2u * (bid / parts);
       bool tk_second = false;
       if (tk) {
@@ -452,8 +473,33 @@ __global__ __launch_bounds__(512) void tgemm_fwd_kernel(
         __syncthreads();
         tk_second = tk_word != 0u;
       }
+      if (part && slots) {
+        // this part's slot, in register order (the layout reduce_parts reads);
+        // blocks wholly outside Y are skipped
+        uint8_t* sp = reinterpret_cast<uint8_t*>(slots + (int64_t)bid * C::kSlotFloats);
+#pragma unroll
+        for (int a = 0; a < MA; ++a) {
+          if (mrow + 32 * a >= M) break;
+#pragma unroll
+          for (int b = 0; b < 2; ++b) {
+            if (n0 + wn * 64 + b * 32 >= N) break;
+            uint32_t o = 16u * (uint32_t)threadIdx.x;
+            asm volatile("" : "+v"(o));
+            const float f = 0.5f * cref[b];
+#pragma unroll
+            for (int i = 0; i < 4; ++i) {
+              f32x4 v;
+#pragma unroll
+              for (int j = 0; j < 4; ++j) v[j] = f * acc[a][b][4 * i + j];
+              *reinterpret_cast<f32x4*>(sp + o + ((a * 2 + b) * 4 + i) * (1024 * NW)) = v;
+            }
+            __builtin_amdgcn_sched_barrier(0);
+          }
+        }
+        continue;
+      }
       uint8_t* ytile = reinterpret_cast<uint8_t*>(Yv) + (mrow * N + n0) * ES;
-      const bool full_m = mrow + 128 <= M;
+      const bool full_m = mrow + 32 * MA <= M;
 #pragma unroll
       for (int b = 0; b < 2; ++b) {
         const int nl = wn * 64 + b * 32 + l32;  // column in the tile
@@ -466,7 +512,7 @@ __global__ __launch_bounds__(512) void tgemm_fwd_kernel(
           uint8_t* yp = ylane;
           int64_t row = mrow + 4 * h;
 #pragma unroll
-          for (int a = 0; a < 4; ++a)
+          for (int a = 0; a < MA; ++a)
 #pragma unroll
             for (int i4 = 0; i4 < 4; ++i4) {
 #pragma unroll
@@ -494,7 +540,7 @@ __global__ __launch_bounds__(512) void tgemm_fwd_kernel(
           const uint32_t pv4 = 4u * pv;
           uint32_t o = (uint32_t)((4 * h) * N + nl) * ES;
 #pragma unroll
-          for (int a = 0; a < 4; ++a)
+          for (int a = 0; a < MA; ++a)
 #pragma unroll
             for (int i4 = 0; i4 < 4; ++i4) {
 #pragma unroll
@@ -502,9 +548,11 @@ __global__ __launch_bounds__(512) void tgemm_fwd_kernel(
                 if constexpr (BF)
                   *reinterpret_cast<uint16_t*>(ytile + o) =
                       __builtin_bit_cast(uint16_t, (__bf16)(f * acc[a][b][4 * i4 + i1]));
-                else
+                else if (whole_lines)
                   __builtin_nontemporal_store(f * acc[a][b][4 * i4 + i1],
                                               reinterpret_cast<float*>(ytile + o));
+                else
+                  *reinterpret_cast<float*>(ytile + o) = f * acc[a][b][4 * i4 + i1];
                 o += pv;
               }
               o += pv4;  // rows 8 i4 + 4 .. 8 i4 + 7 belong to the other k half
@@ -516,7 +564,7 @@ __global__ __launch_bounds__(512) void tgemm_fwd_kernel(
           uint8_t* yp = ylane;
           int64_t row = mrow + 4 * h;
 #pragma unroll
-          for (int a = 0; a < 4; ++a)
+          for (int a = 0; a < MA; ++a)
 #pragma unroll
             for (int i4 = 0; i4 < 4; ++i4) {
 #pragma unroll
@@ -550,60 +598,157 @@ __global__ __launch_bounds__(512) void tgemm_fwd_kernel(
   asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
 }
 
-hipError_t launch_tgemm_fwd(const uint16_t* X, const uint8_t* codes, const float* scales,
-                            int64_t M, int64_t N, int64_t K, int g, void* Y, bool bf16_out,
-                            uint32_t* tickets, hipStream_t stream) {
-  const int64_t tm = (M + kFwdBM - 1) / kFwdBM, tn = (N + kFwdBN - 1) / kFwdBN;
-  const int64_t ntiles = tm * tn;
+// The three tile shapes: workgroups a CU holds; time of a 64-column stage with
+// the chip full and with a CU's workgroup alone on an idle chip (the first is
+// set by the power cap and the shared pipes, the second by a stage's own
+// chain of waits); a slot's write and read.  Measured at g = 128 over 16
+// shapes from 300 x 8512 x 2048 to 16384 x 8512 x 2048.
+struct FwdShape {
+  int bm, bn, per_cu;
+  double full_us, alone_us, slot_us;
+};
+constexpr FwdShape kFwdShapes[3] = {{256, 256, 1, 1.75, 0.95, 0.10},
+                                    {128, 128, 2, 0.98, 0.55, 0.025},
+                                    {64, 128, 3, 0.92, 0.38, 0.0125}};
+constexpr double kFwdLaunchUs = 5.0, kFwdTileUs = 1.0;
+
+struct FwdPlan {
+  int shape = 0;
+  int64_t grid = 0, full = 0, rem = 0;
+  int parts = 1;
+  int64_t slot_bytes() const {
+    return parts > 1 ? rem * parts * kFwdShapes[shape].bm * kFwdShapes[shape].bn * 4 : 0;
+  }
+};
+
+// Tile shape and cut of a forward with slots: least estimated time (whole
+// rounds, the longest run of the leftover tiles, the parts' traffic and
+// reduction).  Large outputs run on 256 x 256 tiles, which read their operands
+// least often (16384 x 8512 x 2048: 520 us, 128 x 128 tiles 570); an output of
+// a few hundred of those leaves CUs idle in its last or only round, where the
+// smaller tiles fill the chip and the workgroups of a CU hide each other's
+// waits (4096 x 2048 x 4096: 256 x 256 tiles cut in two 92 us, 128 x 128
+// tiles 64; 300 x 8512 x 2048: 55 and, on 64 x 128 tiles, 21).
+static FwdPlan fwd_plan(int64_t M, int64_t N, int64_t K, int g) {
   const int cus = current_cu_count();
-  const bool wide = K % 256 == 0;  // code stages of four X stages
-  // Work split over P = cus persistent workgroups: F whole rounds of tiles,
-  // then the R = ntiles mod P remaining tiles cut along K into `parts` runs
-  // of whole trips (kUnroll stages), one per workgroup, when that leaves at
-  // least two parts per tile; otherwise the remaining tiles go whole to the
-  // first R workgroups.
-  const int64_t P = cus;
-  const int64_t F = ntiles / P, R = ntiles % P;
+  const bool wide = K % 256 == 0;
   const int unroll = (wide ? 4 : 1) > g / kFwdBK ? (wide ? 4 : 1) : g / kFwdBK;
   const int64_t trips = K / kFwdBK / unroll;
-  int64_t parts = R > 0 ? P / R : 1;
-  if (parts > trips) parts = trips;
-  if (parts < 1 || bf16_out) parts = 1;  // bfloat16 results are not summed in parts
-  const int64_t extra = R * parts;
-  // two parts per cut tile and tickets given: the first part writes, the
-  // second adds (Y is not cleared; the tickets are, by a fill kernel).  With
-  // few cut tiles the atomics cost little and the second part's wait for the
-  // first (which then finishes at about the same time) would show: atomics.
-  if (parts != 2 || R < kFwdMinTicketTiles || R > kFwdMaxTicketTiles) tickets = nullptr;
-  if (tickets) {
-    hipError_t e = launch_fill_zero_f32(reinterpret_cast<float*>(tickets), 2 * R, stream);
-    if (e != hipSuccess) return e;
-  } else if (parts > 1) {
-    // the cut tiles accumulate atomically: clear their rows of Y first (a
-    // fill kernel, not a memset node, so the call can be captured)
-    const int64_t r0 = F * P / tn * kFwdBM;
-    hipError_t e = launch_fill_zero_f32(static_cast<float*>(Y) + r0 * N, (M - r0) * N, stream);
-    if (e != hipSuccess) return e;
+  FwdPlan best;
+  double best_t = 0;
+  for (int i = 0; i < 3; ++i) {
+    const FwdShape& c = kFwdShapes[i];
+    const int64_t tiles = ((M + c.bm - 1) / c.bm) * ((N + c.bn - 1) / c.bn);
+    if (tiles > 0x7FFFFFFF) continue;  // 32-bit tile numbers
+    const int64_t P = (int64_t)cus * c.per_cu;
+    const int64_t F = tiles / P, R = tiles % P;
+    const int64_t most = R > 0 ? (P / R < trips ? P / R : trips) : 1;
+    for (int64_t k = 1; k <= most; ++k) {
+      const int64_t run = R > 0 ? (trips + k - 1) / k : 0;
+      if (k > 1 && run == (trips + k - 2) / (k - 1)) continue;  // no shorter than k - 1 parts
+      const double load = (double)(R * k) / (double)P;
+      double t = (double)(F * trips * unroll) * c.full_us +
+                 (double)(run * unroll) * (c.alone_us + (c.full_us - c.alone_us) * load) +
+                 (double)(F + (R > 0)) * kFwdTileUs;
+      // (a slot's blocks past M are neither written nor read)
+      if (k > 1)
+        t += kFwdLaunchUs +
+             (double)(R * k) * c.slot_us * (M < c.bm ? (double)((M + 31) / 32 * 32) / c.bm : 1.0);
+      if (best.grid == 0 || t < best_t) {
+        best_t = t;
+        best.shape = i;
+        best.full = F;
+        best.rem = R;
+        best.parts = (int)k;
+        best.grid = F > 0 ? P : R * k;
+      }
+    }
   }
-  const dim3 grid((unsigned)P), block(512);
-  const uint32_t t_n = (uint32_t)tn, fr = (uint32_t)F, xu = (uint32_t)extra,
-                 np = (uint32_t)parts;
-#define TM_FWD_L(GG, SS_, BF_)                                                                 \
-  hipLaunchKernelGGL((tgemm_fwd_kernel<GG, SS_, BF_>), grid, block, 0, stream, X, codes, scales, \
-                     M, N, K, Y, t_n, fr, xu, np, tickets)
-#define TM_FWD(GG)                                                                             \
-  case GG:                                                                                     \
-    if (wide) {                                                                                \
-      if (bf16_out)                                                                            \
-        TM_FWD_L(GG, 4, true);                                                                 \
-      else                                                                                     \
-        TM_FWD_L(GG, 4, false);                                                                \
-    } else {                                                                                   \
-      if (bf16_out)                                                                            \
-        TM_FWD_L(GG, 1, true);                                                                 \
-      else                                                                                     \
-        TM_FWD_L(GG, 1, false);                                                                \
-    }                                                                                          \
+  return best;
+}
+
+int64_t fwd_slot_bytes(int64_t M, int64_t N, int64_t K, int g) {
+  return fwd_plan(M, N, K, g).slot_bytes();
+}
+
+hipError_t launch_tgemm_fwd_parts(const uint16_t* X, const uint8_t* codes, const float* scales,
+                                  int64_t M, int64_t N, int64_t K, int g, void* Y, bool bf16_out,
+                                  uint32_t* tickets, float* slots, bool have_slots,
+                                  hipStream_t stream) {
+  const bool wide = K % 256 == 0;  // code stages of four X stages
+  FwdPlan p;
+  if (have_slots) p = fwd_plan(M, N, K, g);
+  if (p.shape == 0 && (!slots || (tickets && !bf16_out))) {
+    // 256 x 256 tiles whose parts meet in Y: F whole rounds on P = cus
+    // persistent workgroups, then the R = ntiles mod P remaining tiles cut
+    // along K into `parts` runs of whole trips (kUnroll stages), one per
+    // workgroup, when that leaves at least two parts per tile; otherwise the
+    // remaining tiles go whole to the first R workgroups.
+    const int64_t tn = (N + 255) / 256, ntiles = ((M + 255) / 256) * tn;
+    const int64_t P = current_cu_count();
+    const int unroll = (wide ? 4 : 1) > g / kFwdBK ? (wide ? 4 : 1) : g / kFwdBK;
+    const int64_t trips = K / kFwdBK / unroll;
+    FwdPlan q;
+    q.full = ntiles / P;
+    q.rem = ntiles % P;
+    int64_t parts = q.rem > 0 ? P / q.rem : 1;
+    if (parts > trips) parts = trips;
+    if (parts < 1 || bf16_out) parts = 1;  // bfloat16 results are not summed in parts
+    q.parts = (int)parts;
+    q.grid = P;
+    // two parts per cut tile and tickets given: the first part writes, the
+    // second adds (Y is not cleared; the tickets are, by a fill kernel).  With
+    // few cut tiles the atomics cost little and the second part's wait for the
+    // first (which then finishes at about the same time) would show: atomics.
+    if (parts != 2 || q.rem < kFwdMinTicketTiles || q.rem > kFwdMaxTicketTiles) tickets = nullptr;
+    if (tickets || !slots) {
+      p = q;
+      slots = nullptr;
+    }
+    if (tickets) {
+      hipError_t e = launch_fill_zero_f32(reinterpret_cast<float*>(tickets), 2 * q.rem, stream);
+      if (e != hipSuccess) return e;
+    } else if (!slots && p.parts > 1) {
+      // the cut tiles accumulate atomically: clear their rows of Y first (a
+      // fill kernel, not a memset node, so the call can be captured)
+      const int64_t r0 = p.full * P / tn * 256;
+      hipError_t e = launch_fill_zero_f32(static_cast<float*>(Y) + r0 * N, (M - r0) * N, stream);
+      if (e != hipSuccess) return e;
+    }
+  } else {
+    tickets = nullptr;
+  }
+  if (p.parts == 1) slots = nullptr;
+  const FwdShape& c = kFwdShapes[p.shape];
+  const int64_t tn = (N + c.bn - 1) / c.bn, ntiles = ((M + c.bm - 1) / c.bm) * tn;
+  const dim3 grid((unsigned)p.grid);
+  const uint32_t t_n = (uint32_t)tn, fr = (uint32_t)p.full, xu = (uint32_t)(p.rem * p.parts),
+                 np = (uint32_t)p.parts;
+#define TM_FWD_L(GG, SS_, BF_, MA_, NW_)                                                         \
+  hipLaunchKernelGGL((tgemm_fwd_kernel<GG, SS_, BF_, MA_, NW_>), grid, dim3(64 * NW_), 0, stream, \
+                     X, codes, scales, M, N, K, Y, t_n, fr, xu, np, tickets, slots)
+#define TM_FWD_B(GG, SS_, MA_, NW_)       \
+  do {                                    \
+    if (bf16_out)                         \
+      TM_FWD_L(GG, SS_, true, MA_, NW_);  \
+    else                                  \
+      TM_FWD_L(GG, SS_, false, MA_, NW_); \
+  } while (0)
+#define TM_FWD_S(GG, SS_)        \
+  do {                           \
+    if (p.shape == 0)            \
+      TM_FWD_B(GG, SS_, 4, 8);   \
+    else if (p.shape == 1)       \
+      TM_FWD_B(GG, SS_, 2, 4);   \
+    else                         \
+      TM_FWD_B(GG, SS_, 1, 4);   \
+  } while (0)
+#define TM_FWD(GG)      \
+  case GG:              \
+    if (wide)           \
+      TM_FWD_S(GG, 4);  \
+    else                \
+      TM_FWD_S(GG, 1);  \
     break;
   switch (g) {
     TM_FWD(32)
@@ -614,8 +759,20 @@ hipError_t launch_tgemm_fwd(const uint16_t* X, const uint8_t* codes, const float
     default: return hipErrorInvalidValue;
   }
 #undef TM_FWD
+#undef TM_FWD_S
+#undef TM_FWD_B
 #undef TM_FWD_L
-  return hipGetLastError();
+  const hipError_t e = hipGetLastError();
+  if (e != hipSuccess || !slots) return e;
+  return launch_reduce_fwd_parts(slots, p.rem, p.parts, ntiles - p.rem, tn, M, N, Y, bf16_out,
+                                 c.bm, c.bn, stream);
+}
+
+hipError_t launch_tgemm_fwd(const uint16_t* X, const uint8_t* codes, const float* scales,
+                            int64_t M, int64_t N, int64_t K, int g, void* Y, bool bf16_out,
+                            uint32_t* tickets, hipStream_t stream) {
+  return launch_tgemm_fwd_parts(X, codes, scales, M, N, K, g, Y, bf16_out, tickets, nullptr,
+                                false, stream);
 }
 
 }  // namespace tmk

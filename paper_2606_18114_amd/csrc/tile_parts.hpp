@@ -79,5 +79,9 @@ inline TilePlan plan_atomic(int64_t ntiles, int64_t nst, int64_t cus) {
 hipError_t launch_reduce_parts(const float* slots, int64_t rem, int parts, int64_t tile0,
                                int64_t tiles_c, int64_t rows, int64_t cols, void* out,
                                bool bf16_out, bool accumulate, hipStream_t stream);
+// the same for the forward kernel's bm x bn tiles (its wave layouts)
+hipError_t launch_reduce_fwd_parts(const float* slots, int64_t rem, int parts, int64_t tile0,
+                                   int64_t tiles_c, int64_t rows, int64_t cols, void* out,
+                                   bool bf16_out, int bm, int bn, hipStream_t stream);
 
 }  // namespace tmk

@@ -83,6 +83,9 @@ SIGNATURES = {
 
 # the calls of include/tmamba_parts.h
 SIGNATURES_PARTS = {
+    "tm_tgemm_fwd_slots": (ctypes.c_int64, [_I64, _I64, _I64, _I32]),
+    "tm_tgemm_fwd_parts": (ctypes.c_int, [_P, _P, _P, _I64, _I64, _I64, _I32, _P, _I32, _P, _I64,
+                                          _P, _I64, _P]),
     "tm_tgemm_bwd_dx_slots": (ctypes.c_int64, [_I64, _I64, _I64, _I32]),
     "tm_tgemm_bwd_dw_slots": (ctypes.c_int64, [_I64, _I64, _I64]),
     "tm_tgemm_bwd_dx_parts": (ctypes.c_int, [_P, _I32, _P, _P, _P, _I64, _I64, _I64, _I32, _I32,
@@ -290,11 +293,10 @@ def tgemm_fwd(X: torch.Tensor, codes: torch.Tensor, scales: torch.Tensor, g: int
               Y: Optional[torch.Tensor] = None,
               out_dtype: torch.dtype = torch.float32, *,
               workspace: Optional[torch.Tensor] = None) -> torch.Tensor:
-    """Y[M, N] = X . (q * s)^T in float32 (``tm_tgemm_fwd_ws``: the two parts of
-    a cut tile meet through a small workspace, uint8 of at least
-    ``fwd_workspace_bytes()`` bytes; when not given, one kept per stream), or
-    rounded once to bfloat16 (out_dtype=torch.bfloat16,
-    ``tm_tgemm_fwd_bf16``)."""
+    """Y[M, N] = X . (q * s)^T in float32, or rounded once to bfloat16
+    (out_dtype=torch.bfloat16), by ``tm_tgemm_fwd_parts``.  In float32 the two
+    parts of a tile cut in two meet in Y through a given workspace (uint8 of at
+    least ``fwd_workspace_bytes()`` bytes), as in ``tm_tgemm_fwd_ws``."""
     _need(X, "X", _BF16, 2)
     _need(codes, "codes", _U8, 2)
     _need(scales, "scales", _F32, 2)
@@ -308,38 +310,23 @@ def tgemm_fwd(X: torch.Tensor, codes: torch.Tensor, scales: torch.Tensor, g: int
         Y = torch.empty((M, N), dtype=out_dtype, device=X.device)
     _need(Y, "Y", _BF16 if out_dtype == torch.bfloat16 else _F32, 2)
     _shape(Y, "Y", (M, N), X.device)
-    if out_dtype == torch.bfloat16:
-        st = lib().tm_tgemm_fwd_bf16(_ptr(X), _ptr(codes), _ptr(scales), M, N, K, g, _ptr(Y),
-                                     _stream())
-        _check("tm_tgemm_fwd_bf16", st)
-    else:
+    out16 = out_dtype == torch.bfloat16
+    if out16:
+        workspace = None
+    if workspace is not None:
         need = fwd_workspace_bytes()
-        stream = _stream()
-        if workspace is None:
-            workspace = _stream_workspace(X.device, stream, need)
         _need(workspace, "workspace", _U8, 1)
         if workspace.numel() < need:
             raise ValueError(f"workspace has {workspace.numel()} bytes, {need} needed")
         if workspace.device != X.device:
             raise ValueError(f"workspace is on {workspace.device}, the operands on {X.device}")
-        st = lib().tm_tgemm_fwd_ws(_ptr(X), _ptr(codes), _ptr(scales), M, N, K, g, _ptr(Y),
-                                   _ptr(workspace), workspace.numel(), stream)
-        _check("tm_tgemm_fwd_ws", st)
+    slots = _slots(lib().tm_tgemm_fwd_slots(M, N, K, g), X.device)
+    st = lib().tm_tgemm_fwd_parts(_ptr(X), _ptr(codes), _ptr(scales), M, N, K, g, _ptr(Y),
+                                  int(out16), _ptr(workspace),
+                                  0 if workspace is None else workspace.numel(), _ptr(slots),
+                                  0 if slots is None else slots.numel(), _stream())
+    _check("tm_tgemm_fwd_bf16" if out16 else "tm_tgemm_fwd_ws", st)
     return Y
-
-
-_STREAM_WS: dict = {}
-
-
-def _stream_workspace(device: torch.device, stream: int, nbytes: int) -> torch.Tensor:
-    """A small scratch buffer kept per (device, stream): calls on one stream
-    run in order, so they may share it (calls on different streams get
-    their own)."""
-    key = (device.index, stream)
-    ws = _STREAM_WS.get(key)
-    if ws is None or ws.numel() < nbytes:
-        ws = _STREAM_WS[key] = torch.empty(nbytes, dtype=torch.uint8, device=device)
-    return ws
 
 
 _FWD_WS_BYTES: list = []

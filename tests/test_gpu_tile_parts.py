@@ -73,6 +73,34 @@ def test_weight_grad(M, N, K, g):
     assert _rel(acc, ref + 1) <= tol + 2.0 ** -24
 
 
+# (tokens, out features, in features, g): the forward's three tile shapes, cut
+# and whole, with code stages of one and four operand stages
+FORWARD = [(1, 64, 64, 32), (16, 256, 512, 128), (70, 1000, 320, 64), (300, 8512, 2048, 128),
+           (500, 2048, 4096, 128), (1000, 3351, 768, 64), (129, 513, 1536, 512),
+           (2048, 8512, 2048, 128), (4096, 2048, 1024, 256), (3000, 4000, 1024, 32),
+           (33, 8512, 4096, 512), (2100, 4097, 192, 64)]
+
+
+@pytest.mark.parametrize("M,N,K,g", FORWARD)
+def test_forward(M, N, K, g):
+    print(f"[parts] fwd M={M} N={N} K={K} g={g}", flush=True)
+    gen = torch.Generator(device="cuda").manual_seed(1)
+    w = torch.randn((N, K), generator=gen, device="cuda") * 0.02
+    w[:, :g] *= (torch.arange(N, device="cuda") % 3 != 0)[:, None]  # groups of zeros
+    x = torch.randn((M, K), generator=gen, device="cuda").to(torch.bfloat16)
+    codes, s, _, _ = ops.ternarize_pack(w, g, 1e-5)
+    tau = (s + 1e-5).repeat_interleave(g, dim=1)
+    what = (torch.sign(w) * (w.abs() > 0.5 * tau)).double() * s.double().repeat_interleave(g, 1)
+    ref = x.double() @ what.t()
+    Y = torch.full((M, N), float("nan"), device="cuda")
+    ops.tgemm_fwd(x, codes, s, g, Y=Y)
+    # float32 sums of exact products, a rescale (two roundings) per group
+    assert _rel(Y, ref) <= 2.0 ** -24 * (2 * K // g + K ** 0.5)
+    assert torch.equal(Y, ops.tgemm_fwd(x, codes, s, g))
+    Yb = ops.tgemm_fwd(x, codes, s, g, out_dtype=torch.bfloat16)
+    assert torch.equal(Yb, Y.to(torch.bfloat16))
+
+
 def test_float32_gradient_rounding():
     """Ties, infinities, NaN and subnormals round as torch's cast does."""
     _, dy, codes, s, _ = _operands(16, 256, 512, 128)
