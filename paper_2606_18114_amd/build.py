@@ -29,6 +29,7 @@ OBJ = os.path.join(ROOT, "_build")
 SOURCES = [
     "abi.cpp",
     "abi_parts.cpp",
+    "abi_decode16.cpp",
     "ternarize_pack.hip",
     "tgemm_fwd.hip",
     "tgemm_bwd_dx.hip",
@@ -37,6 +38,7 @@ SOURCES = [
     "tile_parts.hip",
     "tgemv.hip",
     "tgemv_b16.hip",
+    "tgemv_rms16.hip",
     "dgemv.hip",
     "mixer.hip",
     "decode_stack.hip",

@@ -48,48 +48,6 @@ tm_status tgemv_checked(const uint16_t* x, const uint8_t* codes, const uint16_t*
   return TM_OK;
 }
 
-// argument checks of the mixer step; workspace NULL: the library's own
-// scratch array (no overlap check needed: no caller array can overlap it)
-// gate_only: the gated float32 output of tm_mixer_gate in place of the
-// normalized bfloat16 one (no norm_w, eps or workspace)
-tm_status mixer_checked(const float* zxbcdt, int32_t B, int32_t nheads, int32_t headdim,
-                        int32_t d_state, uint16_t* conv_state, int32_t* conv_pos,
-                        uint16_t* ssm_state, const float* conv_w, const float* conv_b,
-                        const float* dt_bias, const float* A_log, const float* D,
-                        const float* norm_w, float eps, float* workspace, const void* out,
-                        bool gate_only = false) {
-  if (!zxbcdt || !conv_state || !conv_pos || !ssm_state || !conv_w || !conv_b || !dt_bias ||
-      !A_log || !D || (!gate_only && !norm_w) || !out)
-    return TM_EINVAL;
-  if (!gate_only && (!(eps >= 0.0f) || !std::isfinite(eps))) return TM_EINVAL;
-  if (B < 1 || B > 65535 || nheads < 1 || nheads > 4096 || headdim != 64 || d_state != 128)
-    return TM_ESHAPE;
-  const int64_t di = (int64_t)nheads * headdim, cd = di + 2 * (int64_t)d_state;
-  const int64_t zw = 2 * di + 2 * (int64_t)d_state + nheads;
-  int64_t zb, cb, sb, wb, ob;
-  if (!bytes_of(B, zw, 4, &zb) || !bytes_of((int64_t)B * cd, 4, 2, &cb) ||
-      !bytes_of((int64_t)B * nheads * headdim, d_state, 2, &sb) ||
-      !bytes_of(B, di + nheads, 4, &wb) || !bytes_of(B, di, gate_only ? 4 : 2, &ob))
-    return TM_ESHAPE;
-  if (!aligned(zxbcdt, 4) || !aligned(conv_state, 8) || !aligned(conv_pos, 4) ||
-      !aligned(ssm_state, 16) || !aligned(conv_w, 4) || !aligned(conv_b, 4) ||
-      !aligned(dt_bias, 4) || !aligned(A_log, 4) || !aligned(D, 4) || !aligned(norm_w, 4) ||
-      !aligned(workspace, 4) || !aligned(out, gate_only ? 4 : 2))
-    return TM_EALIGN;
-  const Span outs[5] = {span(conv_state, cb), span(conv_pos, 4), span(ssm_state, sb),
-                        span(workspace, workspace ? wb : 0), span(out, ob)};
-  const Span ins[7] = {span(zxbcdt, zb), span(conv_w, cd * 16), span(conv_b, cd * 4),
-                       span(dt_bias, (int64_t)nheads * 4), span(A_log, (int64_t)nheads * 4),
-                       span(D, (int64_t)nheads * 4), span(norm_w, norm_w ? di * 4 : 0)};
-  for (int i = 0; i < 5; ++i) {
-    for (int j = i + 1; j < 5; ++j)
-      if (overlap(outs[i], outs[j])) return TM_EINVAL;
-    for (const Span& in : ins)
-      if (overlap(outs[i], in)) return TM_EINVAL;
-  }
-  return TM_OK;
-}
-
 }  // namespace
 
 extern "C" {

@@ -154,6 +154,26 @@ hipError_t launch_mixer_gate(const float* zxbcdt, int B, int nheads, uint16_t* c
                              const float* conv_b, const float* dt_bias, const float* A_log,
                              const float* D, float* gated, hipStream_t stream);
 
+// the gated output and the heads' sums of its squares (partial [B, nheads]);
+// the ring position is read and left as it is (launch_tgemv_rms16 moves it on)
+hipError_t launch_mixer_gate_part(const float* zxbcdt, int B, int nheads, uint16_t* conv_state,
+                                  const int* conv_pos, uint16_t* ssm_state, const float* conv_w,
+                                  const float* conv_b, const float* dt_bias, const float* A_log,
+                                  const float* D, float* gated, float* partial,
+                                  hipStream_t stream);
+// launch_tgemv_rms for up to 16 rows at g = 64, 128, 256, the rows' sums of
+// squares given as nparts partial sums each (part [B, nparts]).  part_out (may
+// be NULL): [B, ceil(N / 16)] partial sums of the squares of y as written.
+// advance (may be NULL): a ring position, moved on by one slot.
+constexpr int64_t kRms16MaxK = 4096;  // x of 16 rows in LDS
+hipError_t launch_tgemv_rms16(const float* src, const float* part, int nparts, const float* nw,
+                              float eps, const uint8_t* codes, const uint16_t* s16, int B,
+                              int64_t N, int64_t K, int g, float* y, int accum, float* part_out,
+                              int* advance, hipStream_t stream);
+// part[b] = sum of squares of row b; dst[b] = src[b] unless dst is NULL
+hipError_t launch_rows_sumsq(const float* src, int B, int64_t D, float* dst, float* part,
+                             hipStream_t stream);
+
 // One decode token per batch row (batch 1 .. 4) through a stack of ternary
 // Mamba-2 blocks in one launch with grid barriers (headdim 64, d_state 128,
 // d_conv 4); arrays per block are stacked along a leading layer dimension.

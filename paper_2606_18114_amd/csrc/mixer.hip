@@ -168,6 +168,18 @@ hipError_t launch_mixer_step(const float* zxbcdt, int B, int nheads, uint16_t* c
   return hipGetLastError();
 }
 
+hipError_t launch_mixer_gate_part(const float* zxbcdt, int B, int nheads, uint16_t* conv_state,
+                                  const int* conv_pos, uint16_t* ssm_state, const float* conv_w,
+                                  const float* conv_b, const float* dt_bias, const float* A_log,
+                                  const float* D, float* gated, float* partial,
+                                  hipStream_t stream) {
+  hipLaunchKernelGGL(mixer_ssm_kernel<false>, dim3((unsigned)nheads, (unsigned)B),
+                     dim3(kMxThreads), 0, stream, zxbcdt, nheads, conv_state,
+                     const_cast<int*>(conv_pos), ssm_state, conv_w, conv_b, dt_bias, A_log, D,
+                     gated, partial);
+  return hipGetLastError();
+}
+
 hipError_t launch_mixer_gate(const float* zxbcdt, int B, int nheads, uint16_t* conv_state,
                              int* conv_pos, uint16_t* ssm_state, const float* conv_w,
                              const float* conv_b, const float* dt_bias, const float* A_log,

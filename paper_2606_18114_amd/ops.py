@@ -93,6 +93,15 @@ SIGNATURES_PARTS = {
     "tm_tgemm_bwd_dw_parts": (ctypes.c_int, [_P, _P, _I64, _I64, _I64, _P, _I32, _P, _I64, _P]),
 }
 
+# the calls of include/tmamba_decode16.h
+SIGNATURES_DECODE16 = {
+    "tm_rows_sumsq": (ctypes.c_int, [_P, _I32, _I64, _P, _P, _P]),
+    "tm_tgemv_rms16": (ctypes.c_int, [_P, _P, _I32, _P, ctypes.c_float, _P, _P, _I32, _I64, _I64,
+                                      _I32, _P, _I32, _P, _P, _P]),
+    "tm_mixer_gate_part": (ctypes.c_int, [_P, _I32, _I32, _I32, _I32, _P, _P, _P, _P, _P, _P, _P,
+                                          _P, _P, _P, _P]),
+}
+
 
 class TernaryError(RuntimeError):
     def __init__(self, fn: str, status: int):
@@ -114,7 +123,8 @@ def lib() -> ctypes.CDLL:
                 f"{_LIB_PATH} is missing: build it with `python -m paper_2606_18114_amd.build` "
                 "(or __graft_entry__.build()); there is no fallback implementation")
         L = ctypes.CDLL(_LIB_PATH)
-        for name, (res, args) in (*SIGNATURES.items(), *SIGNATURES_PARTS.items()):
+        for name, (res, args) in (*SIGNATURES.items(), *SIGNATURES_PARTS.items(),
+                                  *SIGNATURES_DECODE16.items()):
             f = getattr(L, name)
             f.restype = res
             f.argtypes = args
@@ -628,6 +638,72 @@ def mixer_gate(zxbcdt: torch.Tensor, conv_state: torch.Tensor, conv_pos: torch.T
                              _ptr(A_log), _ptr(D), _ptr(gated), _stream())
     _check("tm_mixer_gate", st)
     return gated
+
+
+def mixer_gate_part(zxbcdt: torch.Tensor, conv_state: torch.Tensor, conv_pos: torch.Tensor,
+                    ssm_state: torch.Tensor, conv_w: torch.Tensor, conv_b: torch.Tensor,
+                    dt_bias: torch.Tensor, A_log: torch.Tensor, D: torch.Tensor,
+                    gated: torch.Tensor, partial: torch.Tensor) -> None:
+    """mixer_gate that also writes the heads' sums of the squares of gated
+    (partial float32 [B, nheads]) and leaves conv_pos to ``tgemv_rms16``."""
+    B, H, P, N, di, dev = _mixer_args(
+        zxbcdt, conv_state, conv_pos, ssm_state, A_log,
+        ((conv_w, "conv_w"), (conv_b, "conv_b"), (dt_bias, "dt_bias"), (D, "D")))
+    _need(gated, "gated", _F32, 2)
+    _shape(gated, "gated", (B, di), dev)
+    _need(partial, "partial", _F32, 2)
+    _shape(partial, "partial", (B, H), dev)
+    st = lib().tm_mixer_gate_part(_ptr(zxbcdt), B, H, P, N, _ptr(conv_state), _ptr(conv_pos),
+                                  _ptr(ssm_state), _ptr(conv_w), _ptr(conv_b), _ptr(dt_bias),
+                                  _ptr(A_log), _ptr(D), _ptr(gated), _ptr(partial), _stream())
+    _check("tm_mixer_gate_part", st)
+
+
+def rows_sumsq(src: torch.Tensor, part: torch.Tensor, dst: Optional[torch.Tensor] = None) -> None:
+    """part float32 [B, 1] = sums of squares of the rows of src float32
+    [B, D]; dst (optional, [B, D]) = src."""
+    _need(src, "src", _F32, 2)
+    B, D = src.shape
+    _need(part, "part", _F32, 2)
+    _shape(part, "part", (B, 1), src.device)
+    if dst is not None:
+        _need(dst, "dst", _F32, 2)
+        _shape(dst, "dst", (B, D), src.device)
+    st = lib().tm_rows_sumsq(_ptr(src), B, D, _ptr(dst), _ptr(part), _stream())
+    _check("tm_rows_sumsq", st)
+
+
+RMS16_MAX_K = 4096  # columns tm_tgemv_rms16 takes
+
+
+def tgemv_rms16(src: torch.Tensor, part: torch.Tensor, codes: torch.Tensor,
+                scales_f16: torch.Tensor, g: int, norm_w: torch.Tensor, eps: float,
+                y: torch.Tensor, accumulate: bool = False,
+                part_out: Optional[torch.Tensor] = None,
+                advance: Optional[torch.Tensor] = None) -> torch.Tensor:
+    """tgemv_rms for up to 16 rows at g = 64, 128 or 256, the rows' sums of
+    squares given as partial sums (part float32 [B, P]).  part_out (optional,
+    float32 [B, ceil(N/16)]) receives those of y as written; advance
+    (optional): a mixer's conv_pos, moved on by one slot."""
+    _need(codes, "codes", _U8, 2)
+    N = codes.shape[0]
+    B, K, y = _rms_args(src, norm_w, y, N)
+    _need(scales_f16, "scales_f16", _F16, 2)
+    _shape(codes, "codes", (N, K // 4), src.device)
+    _shape(scales_f16, "scales_f16", (N, _groups(K, g)), src.device)
+    _need(part, "part", _F32, 2)
+    _shape(part, "part", (B, part.shape[1]), src.device)
+    if part_out is not None:
+        _need(part_out, "part_out", _F32, 2)
+        _shape(part_out, "part_out", (B, (N + 15) // 16), src.device)
+    if advance is not None:
+        _need(advance, "advance", (torch.int32,), 1)
+        _shape(advance, "advance", (1,), src.device)
+    st = lib().tm_tgemv_rms16(_ptr(src), _ptr(part), part.shape[1], _ptr(norm_w), eps,
+                              _ptr(codes), _ptr(scales_f16), B, N, K, g, _ptr(y),
+                              int(bool(accumulate)), _ptr(part_out), _ptr(advance), _stream())
+    _check("tm_tgemv_rms16", st)
+    return y
 
 
 def mixer_workspace(B: int, nheads: int, device) -> torch.Tensor:

@@ -209,6 +209,10 @@ class Mamba2Decoder:
     buffers, so a token can be captured once as a HIP graph (``capture``) and
     replayed.
 
+    or, for batches the fused form does not take (no kept layers, g 64, 128 or
+    256), its three launches with the rows' sums of squares passed from one to
+    the next: tm_tgemv_rms16, tm_mixer_gate_part, tm_tgemv_rms16;
+
     or the whole stack in one launch (``tm_mamba2_decode_token``: the three
     phases of every block separated by grid barriers instead of launches;
     batch 1 .. 4, kept blocks included).
@@ -249,6 +253,12 @@ class Mamba2Decoder:
         if fused and not fits:
             raise ValueError(f"batch {batch} does not fit the fused decode at g = {g}")
         self.fused = fits if fused is None else bool(fused)
+        # a token at batches past the fused form's: its three launches with the
+        # sums of squares passed along (fused=False keeps the unfused form, as
+        # does layer_step, which stands alone)
+        self.fused16 = (fused is None and not self.fused and not self.keep
+                        and 1 <= batch <= 16 and g in (64, 128, 256)
+                        and max(d_model, self.d_inner) <= ops.RMS16_MAX_K)
         st_ok = stack_fits(batch, d_model, nheads, g) and len(self.keep) <= MAX_KEPT_STACK
         if stack and not st_ok:
             raise ValueError(f"the one-launch stack decode needs at most {MAX_KEPT_STACK} "
@@ -321,6 +331,11 @@ class Mamba2Decoder:
         self.arena["final_w"] = self.final_norm
         self.stack_ws = (ops.mamba2_decode_workspace(d_model, nheads, dev, batch)
                          if self.stack else None)
+        if self.fused16:
+            self.part_emb = torch.empty((batch, 1), dtype=torch.float32, device=dev)
+            self.part_res = torch.empty((batch, (d_model + 15) // 16), dtype=torch.float32,
+                                        device=dev)
+            self.part_gate = torch.empty((batch, nheads), dtype=torch.float32, device=dev)
         self.graph = None
 
     def set_states(self, l: int, conv: torch.Tensor, ssm: torch.Tensor, pos: int = 0) -> None:
@@ -352,9 +367,9 @@ class Mamba2Decoder:
         the residual.  Unfused: pre-norm (taking the previous layer's output
         into the residual), in_proj, mixer step, out_proj into ``y``."""
         lay = self.layers[l]
+        mp = lay["mixer"]
         if l == 0:
             self.residual.copy_(self.emb)
-        mp = lay["mixer"]
         if self.fused:
             self._proj_rms(lay, "in", self.residual, lay["pre"], self.zx[0], False)
             ops.mixer_gate(self.zx[0], lay["conv"], lay["pos"], lay["ssm"], mp["conv_w"],
@@ -369,6 +384,23 @@ class Mamba2Decoder:
                        workspace=self.ws, out=self.m[0])
         self._proj(lay, "out", self.m, self.y)
 
+    def _token16(self) -> None:
+        """Every layer of a token on the batched fused launches: each one
+        leaves the sums of squares the next one normalizes its rows with."""
+        part = self.part_emb
+        ops.rows_sumsq(self.emb, part, dst=self.residual)
+        for lay in self.layers:
+            mp, (_, ic, isc), (_, oc, osc) = lay["mixer"], lay["in"], lay["out"]
+            ops.tgemv_rms16(self.residual, part, ic[0], isc[0], self.g, lay["pre"], self.eps,
+                            self.zx[0])
+            ops.mixer_gate_part(self.zx[0], lay["conv"], lay["pos"], lay["ssm"], mp["conv_w"],
+                                mp["conv_b"], mp["dt_bias"], mp["A_log"], mp["D"], self.gated,
+                                self.part_gate)
+            part = self.part_res
+            ops.tgemv_rms16(self.gated, self.part_gate, oc[0], osc[0], self.g, mp["norm_w"],
+                            self.eps, self.residual, accumulate=True, part_out=part,
+                            advance=lay["pos"])
+
     def token_stack(self) -> torch.Tensor:
         """One token per batch row through every block in a single launch."""
         a = {k: self.arena[k] for k in ops.STACK_FIELDS}
@@ -382,10 +414,13 @@ class Mamba2Decoder:
         layer; returns ``x_out`` = final norm of the residual (bfloat16)."""
         if self.stack:
             return self.token_stack()
-        for l in range(self.L):
-            self.layer_step(l)
-        ops.residual_rmsnorm(self.residual, None if self.fused else self.y[0], self.final_norm,
-                             self.eps, x=self.x_out)
+        if self.fused16:
+            self._token16()
+        else:
+            for l in range(self.L):
+                self.layer_step(l)
+        pending = None if self.fused or self.fused16 else self.y[0]
+        ops.residual_rmsnorm(self.residual, pending, self.final_norm, self.eps, x=self.x_out)
         return self.x_out
 
     def capture(self) -> None:
@@ -410,7 +445,7 @@ class Mamba2Decoder:
         # out_proj; then the residual copy and the final norm
         if self.stack:
             return 2
-        return (3 if self.fused else 5) * self.L + 2
+        return (3 if self.fused or self.fused16 else 5) * self.L + 2
 
     def bytes_per_token(self) -> float:
         """Algorithmic HBM bytes of one token: packed or float16 projection

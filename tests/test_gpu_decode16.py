@@ -1,0 +1,101 @@
+"""The batched fused decode launches (tm_tgemv_rms16, tm_mixer_gate_part):
+the projection against float64 over the batches, group sizes and edges of its
+blocks, and whole tokens against the unfused decode, eager and replayed."""
+
+import pytest
+
+torch = pytest.importorskip("torch")
+
+from paper_2606_18114_amd import ops  # noqa: E402
+from paper_2606_18114_amd.stack import Mamba2Decoder  # noqa: E402
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.fixture(autouse=True)
+def _gpu():
+    if not torch.cuda.is_available():
+        pytest.skip("no GPU")
+
+
+def _packed(gen, N, K, g):
+    w = torch.randn((N, K), generator=gen, device="cuda") * 0.02
+    codes, s, s16, _ = ops.ternarize_pack(w, g, 1e-5)
+    tau = (s + 1e-5).repeat_interleave(g, dim=1)
+    q = (torch.sign(w) * (w.abs() > 0.5 * tau)).double()
+    return codes, s16, q * s16.double().repeat_interleave(g, 1)
+
+
+# (B, N, K, g): one row and all sixteen, one block and one output, blocks of
+# two and ragged ones, fewer groups than waves, several rounds of chunks
+@pytest.mark.parametrize("B,N,K,g", [(1, 1, 64, 64), (5, 130, 256, 256), (16, 2048, 4096, 128),
+                                     (9, 8512, 2048, 128), (12, 8500, 512, 64),
+                                     (16, 17, 4096, 256), (7, 6170, 320, 64)])
+@pytest.mark.parametrize("accumulate", [False, True])
+def test_projection(B, N, K, g, accumulate):
+    print(f"[decode16] B={B} N={N} K={K} g={g} accumulate={accumulate}", flush=True)
+    gen = torch.Generator(device="cuda").manual_seed(B + N)
+    codes, s16, what = _packed(gen, N, K, g)
+    src = torch.randn((B, K), generator=gen, device="cuda")
+    nw = 1 + 0.1 * torch.randn(K, generator=gen, device="cuda")
+    P = 3
+    cuts = [0, K // 4, K // 2, K]
+    part = torch.stack([src[:, a:b].square().sum(1) for a, b in zip(cuts, cuts[1:])], 1)
+    y0 = torch.randn((B, N), generator=gen, device="cuda")
+    y = y0.clone()
+    part_out = torch.full((B, (N + 15) // 16), float("nan"), device="cuda")
+    pos = torch.tensor([3], dtype=torch.int32, device="cuda")
+    ops.tgemv_rms16(src, part.contiguous(), codes, s16, g, nw, 1e-5, y, accumulate=accumulate,
+                    part_out=part_out, advance=pos)
+    assert P == part.shape[1] and int(pos) == 0
+    r = 1 / torch.sqrt(part.sum(1) / K + 1e-5)
+    x = (src * r[:, None] * nw).to(torch.bfloat16).double()
+    ref = x @ what.t() + (y0.double() if accumulate else 0)
+    mag = x.abs() @ what.abs().t() + y0.double().abs()
+    # float32 sums of exact products; an x on the edge of its bfloat16
+    # rounding (another order of the sums of squares) may move by 2^-8
+    err = (y.double() - ref).abs()
+    assert bool((err <= (K ** 0.5 * 2.0 ** -23 + 2.0 ** -9 / K ** 0.5) * mag).all())
+    sq = torch.zeros((B, (N + 15) // 16 * 16), device="cuda", dtype=torch.float64)
+    sq[:, :N] = y.double().square()
+    assert torch.allclose(part_out.double(), sq.view(B, -1, 16).sum(2), rtol=2e-6)
+
+
+@pytest.mark.parametrize("B,d_model,heads,g", [(5, 256, 8, 64), (16, 512, 16, 128),
+                                               (12, 768, 24, 256), (8, 2048, 64, 128)])
+def test_token_matches_the_unfused_decode(B, d_model, heads, g):
+    print(f"[decode16] token B={B} d_model={d_model} heads={heads} g={g}", flush=True)
+    L, di = 3, 64 * heads
+    cd = di + 256
+
+    def build(**kw):
+        def weight(side, l):
+            n, k = (2 * di + 256 + heads, d_model) if side == "in" else (d_model, di)
+            gw = torch.Generator(device="cuda").manual_seed(100 * l + (side == "in"))
+            return torch.randn((n, k), generator=gw, device="cuda") * 0.02
+
+        def mixer(l):
+            gm = torch.Generator(device="cuda").manual_seed(1000 + l)
+            u = lambda *s: torch.rand(s, generator=gm, device="cuda")  # noqa: E731
+            return dict(conv_w=u(cd, 4) - 0.5, conv_b=u(cd) - 0.5, dt_bias=u(heads) - 4,
+                        A_log=torch.log(1 + 15 * u(heads)), D=u(heads), norm_w=0.5 + u(di))
+        return Mamba2Decoder(weight, mixer, lambda l: torch.full((d_model,), 1.0 + 0.1 * l), L,
+                             d_model, heads, g=g, batch=B, **kw)
+    a, b = build(), build(fused=False)
+    assert a.fused16 and not a.fused and not b.fused16 and not b.stack
+    gen = torch.Generator(device="cuda").manual_seed(7)
+    for step in range(5):
+        e = torch.randn((B, d_model), generator=gen, device="cuda")
+        a.emb.copy_(e)
+        b.emb.copy_(e)
+        if step == 2:  # the state goes on through replays of a capture
+            a.capture()
+        xa = (a.replay() if step >= 2 else a.token()).float()
+        xb = b.token().float()
+        # each of the 2 L activations handed on may round to the other
+        # bfloat16 neighbour: 2^-9 each, at most as independent errors
+        assert float((xa - xb).norm() / xb.norm()) <= 2.0 ** -8 * (2 * L) ** 0.5
+        for la, lb in zip(a.layers, b.layers):
+            assert torch.equal(la["pos"], lb["pos"]) and int(la["pos"]) == (step + 1) % 4
+            d = (la["ssm"].float() - lb["ssm"].float()).norm() / lb["ssm"].float().norm()
+            assert float(d) <= 2.0 ** -8 * (2 * L) ** 0.5
