@@ -138,6 +138,12 @@ __global__ __launch_bounds__(64 * NW, 2) void tgemm_fwd_kernel(
     void* __restrict__ Yv, uint32_t tiles_n, uint32_t full_rounds, uint32_t extra_units,
     uint32_t parts, uint32_t* __restrict__ tickets, float* __restrict__ slots) {
   using C = FwdCfg<G, SS, MA, NW>;
+  // the smaller tiles have the registers for a second accumulator: each
+  // group's products add up by themselves and join the total by one fused
+  // multiply-add, which rounds once per group where the rescaled accumulator
+  // rounds at every MFMA (relative error over K = 256 .. 3584: 3e-8 to 1.1e-7
+  // against 5e-8 to 1.6e-7)
+  constexpr bool kTwo = MA <= 2;
   constexpr int kFwdXStage = C::kXStage, kFwdBM = C::kBM, kFwdBN = C::kBN;
   __shared__ __attribute__((aligned(1024))) uint8_t lds[C::kLds];
   __shared__ uint32_t tk_word;  // arrival order of this workgroup at its cut tile
@@ -328,13 +334,19 @@ __global__ __launch_bounds__(64 * NW, 2) void tgemm_fwd_kernel(
     unit_of(u, tile, s0, s1, part);
     tile_rows(tile, m0, n0);
 
-    f32x16 acc[MA][2];
+    f32x16 acc[MA][2], tot[kTwo ? MA : 1][2];
 #pragma unroll
     for (int a = 0; a < MA; ++a)
 #pragma unroll
       for (int b = 0; b < 2; ++b)
 #pragma unroll
         for (int i = 0; i < 16; ++i) acc[a][b][i] = 0.f;
+#pragma unroll
+    for (int a = 0; a < (kTwo ? MA : 1); ++a)
+#pragma unroll
+      for (int b = 0; b < 2; ++b)
+#pragma unroll
+        for (int i = 0; i < 16; ++i) tot[a][b][i] = 0.f;
     float cref[2] = {0.f, 0.f};
     uint32_t msk[2] = {0u, 0u};
 
@@ -389,22 +401,45 @@ __global__ __launch_bounds__(64 * NW, 2) void tgemm_fwd_kernel(
 #pragma unroll
           for (int b = 0; b < 2; ++b) {
             const float sv = sc[b][t / 2];
+            if constexpr (kTwo) {
+              r[b] = cref[b];  // the scale of the group that ended
+              cref[b] = sv;
+              continue;
+            }
             const bool nz = sv != 0.f;
             msk[b] = nz ? 0xFFFFFFFFu : 0u;
-            const float ratio = cref[b] * __builtin_amdgcn_rcpf(nz ? sv : 1.f);
+            // c / s to within half an ulp: the approximate reciprocal's error,
+            // the same for every output of the row, would add up over the groups
+            const float den = nz ? sv : 1.f, rc = __builtin_amdgcn_rcpf(den);
+            float ratio = cref[b] * rc;
+            const float rest = __builtin_fmaf(-den, ratio, cref[b]);
+            ratio = fabsf(rest) < __builtin_inff() ? __builtin_fmaf(rest, rc, ratio) : ratio;
             r[b] = (nz && cref[b] != 0.f) ? ratio : 1.f;
             cref[b] = nz ? sv : cref[b];
           }
         }
         bf16x8 bop[2];
-        decode_half_pair_rt(u32x2{cw[0][t] & msk[0], cw[1][t] & msk[1]}, hs, bop[0], bop[1]);
+        if constexpr (kTwo)
+          decode_half_pair_rt(u32x2{cw[0][t], cw[1][t]}, hs, bop[0], bop[1]);
+        else
+          decode_half_pair_rt(u32x2{cw[0][t] & msk[0], cw[1][t] & msk[1]}, hs, bop[0], bop[1]);
         bf16x8 anext[MA];
         if (t < 3) read_a(t + 1, anext);
 #pragma unroll
         for (int a = 0; a < MA; ++a) {
 #pragma unroll
           for (int b = 0; b < 2; ++b) {
-            if (start) acc[a][b] *= r[b];
+            if (start) {
+              if constexpr (kTwo) {
+#pragma unroll
+                for (int i = 0; i < 16; ++i) {
+                  tot[a][b][i] = __builtin_fmaf(r[b], acc[a][b][i], tot[a][b][i]);
+                  acc[a][b][i] = 0.f;
+                }
+              } else {
+                acc[a][b] *= r[b];
+              }
+            }
             acc[a][b] = mfma32(acur[a], bop[b], acc[a][b]);
           }
         }
@@ -449,6 +484,15 @@ __global__ __launch_bounds__(64 * NW, 2) void tgemm_fwd_kernel(
     // of a tile add their partial sums with float32 atomics.
     {
       const int64_t mrow = m0 + wm * 32 * MA;
+      if constexpr (kTwo) {
+#pragma unroll
+        for (int a = 0; a < MA; ++a)
+#pragma unroll
+          for (int b = 0; b < 2; ++b)
+#pragma unroll
+            for (int i = 0; i < 16; ++i)
+              acc[a][b][i] = 0.5f * __builtin_fmaf(cref[b], acc[a][b][i], tot[a][b][i]);
+      }
       constexpr int ES = BF ? 2 : 4;  // bytes per output element
       // two-part cut tile with tickets: which part arrives first
       const bool tk = !BF && NW == 8 && part && tickets != nullptr;
@@ -485,7 +529,7 @@ __global__ __launch_bounds__(64 * NW, 2) void tgemm_fwd_kernel(
             if (n0 + wn * 64 + b * 32 >= N) break;
             uint32_t o = 16u * (uint32_t)threadIdx.x;
             asm volatile("" : "+v"(o));
-            const float f = 0.5f * cref[b];
+            const float f = kTwo ? 1.f : 0.5f * cref[b];
 #pragma unroll
             for (int i = 0; i < 4; ++i) {
               f32x4 v;
@@ -504,7 +548,7 @@ __global__ __launch_bounds__(64 * NW, 2) void tgemm_fwd_kernel(
       for (int b = 0; b < 2; ++b) {
         const int nl = wn * 64 + b * 32 + l32;  // column in the tile
         if (n0 + nl >= N) continue;
-        const float f = 0.5f * cref[b];
+        const float f = kTwo ? 1.f : 0.5f * cref[b];
         uint8_t* ylane = ytile + ((int64_t)(4 * h) * N + nl) * ES;
         if (!BF && part) {
           int64_t pv = N * 4;
