@@ -84,6 +84,7 @@ __device__ __forceinline__ void mixer_head_step(
   const int d_inner = nheads * kMxP;
   __shared__ float u[kMxP + 2 * kMxN];  // x of the head, then B, then C (after SiLU)
   __shared__ float wsum[kMxThreads / 64];
+  __shared__ float step[2];             // dt', decay
   const int p = tid >> 2, q = tid & 3;
 
   // convolution: local channel i < 64 is x channel 64 h + i, then the B/C
@@ -127,10 +128,21 @@ __device__ __forceinline__ void mixer_head_step(
     // the slot nobody reads; the shared B/C channels are written by head 0
     if (i < kMxP || h == 0) conv_b[(int64_t)c * 4 + pos] = f2h(xin[t]);
   }
+  // dt' and the decay, once per head, by the last wave while the first takes
+  // its second channels (every thread doing it after the barrier was 150
+  // instructions of each wave's chain); the gate's SiLU also before the barrier
+  if (tid >= kMxThreads - 64) {
+    const float dtp0 = mx_softplus(dt_raw + dtb);
+    const float a0 = expf(-dtp0 * expf(alog));
+    if (tid == kMxThreads - 64) {
+      step[0] = dtp0;
+      step[1] = a0;
+    }
+  }
+  const float gz = mx_silu(zp);
   __syncthreads();
 
-  const float dtp = mx_softplus(dt_raw + dtb);
-  const float a = expf(-dtp * expf(alog));
+  const float dtp = step[0], a = step[1];
   const float xp = u[p];
   const float dx = dtp * xp;
   uint16_t* sp = ssm_h + p * kMxN + 32 * q;
@@ -154,7 +166,7 @@ __device__ __forceinline__ void mixer_head_step(
   y += __uint_as_float(lane_xchg<1>(__float_as_uint(y)));
   y += __uint_as_float(lane_xchg<2>(__float_as_uint(y)));
   y = __builtin_fmaf(dskip, xp, y);
-  const float g = y * mx_silu(zp);
+  const float g = y * gz;
   if (q == 0) st_f32<COH>(gated_b + h * kMxP + p, g);
   if (part == nullptr) return;
   // sum of g^2 over the head's 64 channels: each channel counted once (q = 0)
