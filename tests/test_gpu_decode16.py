@@ -1,5 +1,5 @@
-"""The batched fused decode launches (tm_tgemv_rms16, tm_mixer_gate_part):
-the projection against float64 over the batches, group sizes and edges of its
+"""The batched decode launches (tm_tgemv_rms16, tm_mixer_gate_part, tm_tgemv):
+the projections against float64 over the batches, group sizes and edges of its
 blocks, and whole tokens against the unfused decode, eager and replayed."""
 
 import pytest
@@ -99,3 +99,26 @@ def test_token_matches_the_unfused_decode(B, d_model, heads, g):
             assert torch.equal(la["pos"], lb["pos"]) and int(la["pos"]) == (step + 1) % 4
             d = (la["ssm"].float() - lb["ssm"].float()).norm() / lb["ssm"].float().norm()
             assert float(d) <= 2.0 ** -8 * (2 * L) ** 0.5
+
+
+# (matrices, B, N, K, g): past four 16-row blocks per CU x is copied to LDS;
+# one, two and four blocks per wave, K below, at and past a window of columns,
+# rounds with one group and with sixteen, ragged rows and matrices
+@pytest.mark.parametrize("count,B,N,K,g", [(3, 9, 5500, 4160, 64), (2, 16, 8500, 4608, 512),
+                                           (1, 12, 16500, 64, 64), (1, 16, 262149, 64, 64),
+                                           (1, 10, 524300, 128, 128), (4, 16, 4300, 2048, 256),
+                                           (4, 11, 4300, 2304, 128), (1, 16, 1000, 8192, 256)])
+def test_batched_gemv(count, B, N, K, g):
+    print(f"[decode16] gemv {count} x B={B} N={N} K={K} g={g}", flush=True)
+    gen = torch.Generator(device="cuda").manual_seed(N + K)
+    packed = [_packed(gen, N, K, g) for _ in range(count)]
+    x = torch.randn((count, B, K), generator=gen, device="cuda").to(torch.bfloat16)
+    codes = torch.stack([p[0] for p in packed])
+    s16 = torch.stack([p[1] for p in packed])
+    y = torch.full((count, B, N), float("nan"), device="cuda")
+    ops.tgemv(x, codes, s16, g, y=y)
+    for i in range(count):
+        ref = x[i].double() @ packed[i][2].t()
+        mag = x[i].double().abs() @ packed[i][2].abs().t()
+        # exact products, float32 sums of at most K of them
+        assert bool(((y[i].double() - ref).abs() <= (K + 2) * 2.0 ** -24 * mag + 1e-30).all())
