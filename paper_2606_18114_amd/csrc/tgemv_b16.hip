@@ -31,7 +31,7 @@ constexpr int kB16Cols = 1024;  // columns of a row in flight together
 
 // W: waves; KMAX: columns of x in LDS
 template <int G, int W, int KMAX>
-__global__ __launch_bounds__(64 * W) void tgemv_b16_kernel(const uint16_t* __restrict__ x,
+__global__ __launch_bounds__(64 * W, 4) void tgemv_b16_kernel(const uint16_t* __restrict__ x,
                                                            const uint8_t* __restrict__ codes,
                                                            const uint16_t* __restrict__ s16,
                                                            int B, int N, int K, int wgs, int bpw,
@@ -138,6 +138,11 @@ __global__ __launch_bounds__(64 * W) void tgemv_b16_kernel(const uint16_t* __res
 #pragma unroll
     for (int i = 0; i < 4; ++i) {
       if (i >= bpw) break;
+      float part[4][4];  // sums of every fourth group: short chains round less
+#pragma unroll
+      for (int t = 0; t < 4; ++t)
+#pragma unroll
+        for (int e = 0; e < 4; ++e) part[t][e] = 0.f;
       for (int r0 = 0; r0 < kw; r0 += kB16Cols) {
         Round nxt;
         const bool last = r0 + kB16Cols >= kw;
@@ -158,11 +163,15 @@ __global__ __launch_bounds__(64 * W) void tgemv_b16_kernel(const uint16_t* __res
             const int g = s / kSpg;
             const float sv = h2f((uint16_t)__shfl((int)cur.sc[g / 4], 16 * (g % 4) + n, 64));
 #pragma unroll
-            for (int e = 0; e < 4; ++e) tot[i][e] = __builtin_fmaf(acc[e], sv, tot[i][e]);
+            for (int e = 0; e < 4; ++e)
+              part[g % 4][e] = __builtin_fmaf(acc[e], sv, part[g % 4][e]);
           }
         }
         cur = nxt;
       }
+#pragma unroll
+      for (int e = 0; e < 4; ++e)
+        tot[i][e] += (part[0][e] + part[1][e]) + (part[2][e] + part[3][e]);
     }
   }
   // lane (kq, n) holds batch rows 4 kq + e of weight row n; the codes decode to 2q
