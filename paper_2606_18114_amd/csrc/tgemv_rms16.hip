@@ -114,21 +114,19 @@ __global__ __launch_bounds__(64 * kR16Waves) void tgemv_rms16_kernel(
     *reinterpret_cast<u32x2*>(lds + (uint32_t)row * (2u * K) + 16u * u + 8u * (q & 1)) =
         u32x2{o[0], o[1]};
   };
-  // the rows' 1 / rms (while loads of src are in flight): the partial sums add
-  // up in float64 and one Newton step takes the float32 estimate to its last
-  // bit, since an error here moves bfloat16 roundings of a whole row
+  // the rows' 1 / rms (while loads of src are in flight)
   auto row_scales = [&]() {
     const int row = tid / kPr, l = tid % kPr;
-    double s = 0.0;
+    float s = 0.f;
     if (row < B)
-      for (int i = l; i < nparts; i += kPr) s += (double)part[(int64_t)row * nparts + i];
-    s = group_sum_f64<64>(s);
-    const double ms = s * (1.0 / (double)K) + (double)eps;
-    const float r0 = 1.f / sqrtf((float)ms);
-    const double d = (double)r0;
-    const float r1 = (float)(d + 0.5 * d * (1.0 - ms * d * d));
-    // (a mean square of 0, infinity or NaN has nothing to refine)
-    if (l == 0) rs[row] = r0 > 0.f && r0 < __builtin_inff() ? r1 : r0;
+      for (int i = l; i < nparts; i += kPr) s += part[(int64_t)row * nparts + i];
+    s += __uint_as_float(lane_xchg<1>(__float_as_uint(s)));
+    s += __uint_as_float(lane_xchg<2>(__float_as_uint(s)));
+    s += __uint_as_float(lane_xchg<4>(__float_as_uint(s)));
+    s += __uint_as_float(lane_xchg<8>(__float_as_uint(s)));
+    s += __uint_as_float(lane_xchg<16>(__float_as_uint(s)));
+    s += __uint_as_float(lane_xchg<32>(__float_as_uint(s)));
+    if (l == 0) rs[row] = 1.f / sqrtf(s / (float)K + eps);
     if (advance && blockIdx.x == 0 && tid == 0) *advance = (*advance + 1) & 3;
     __syncthreads();
   };
