@@ -25,6 +25,11 @@
 // cleared dW.  Whole tiles are written with plain stores (read-add-write
 // when accumulating).
 //
+// Bound: the matrix cores under the power cap where tiles are many (16384
+// tokens of 2048 -> 8512: 464 us, 1.23 PFLOP/s; 637 us while every stage first
+// waited for its own LDS reads), the slots' traffic and the reduction where
+// they are few (2048 tokens: 81 + 6 us, 131 with atomics).
+//
 // The direct-to-LDS loads are issued from inline assembly, so the compiler
 // neither tracks nor waits for them; each wave issues exactly eight per
 // stage and counts them itself (vector-memory operations retire in order).

@@ -28,9 +28,10 @@
 //     receives one column of 4 consecutive rows.
 //
 // Work split (persistent, one workgroup per CU): the T output tiles are dealt
-// round-robin, whole, T / P per workgroup; the T % P remaining tiles are each
-// cut along the contraction into P / (T % P) parts that are added into dX
-// (cleared first) with float32 atomics.
+// round-robin, whole, T / P per workgroup; the T % P remaining tiles are cut
+// along the contraction into parts that meet in slots of a caller's buffer
+// (tile_parts.hpp), or, without one, by float32 atomics into a cleared dX.
+// (1000 x 3352 -> 768: 12 tiles, 136 us whole, 28 + 6 us cut in nine.)
 //
 // The direct-to-LDS loads are issued from inline assembly, so the compiler
 // neither tracks nor waits for them; each wave issues exactly seven per stage

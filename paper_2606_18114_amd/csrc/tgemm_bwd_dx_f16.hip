@@ -28,7 +28,8 @@
 // direct-to-LDS loads issued three stages ahead, the codes decoded one stage
 // ahead into a double-buffered float16 plane read back by ds_read_b64_tr_b16,
 // 32 MFMAs per wave and stage.  Work split as there: whole tiles round-robin,
-// the remainder cut along N and added with float32 atomics into a cleared dX.
+// the remainder cut along N into parts that meet in slots (2048 tokens of
+// 8512 -> 2048: 64 tiles, 195 us whole, 73 + 13 us cut in four).
 // The weight plane is built from the codes with one shift and one AND per two
 // codes (the float16 values 2q) and one packed float16 multiply by the scale.
 #include "dx_common.hpp"

@@ -1,15 +1,17 @@
 // Ternary forward GEMM (paper Sec. 3.1): Y[M, N] = X[M, K] . What[N, K]^T,
 // What = s * q, on the gfx950 matrix cores (v_mfma_f32_32x32x16_bf16).
 //
-// Persistent kernel: one workgroup of 8 waves per CU walks 256 x 256 output
-// tiles (2 x 4 waves, 128 x 64 outputs per wave).  Consecutive tiles of one
-// round go to the same XCD, so its workgroups share the rows of X through
-// that XCD's L2.  Tiles left over after the whole rounds (fewer than one
-// per workgroup) are cut along K into parts, one per workgroup, which add
-// their partial sums into Y with float32 atomics (those rows of Y are
-// cleared by a fill kernel first).  Without the cut, a shape with a few
-// tiles more than workgroups would take two full rounds; with it the last
-// round is spread over all CUs (2048 tokens of in_proj: 27% faster).
+// Persistent kernel in three tile shapes (the rule and its figures: fwd_plan):
+// one workgroup of 8 waves per CU on 256 x 256 output tiles (2 x 4 waves, 128
+// x 64 outputs per wave), or two or three workgroups of 4 waves on 128 x 128
+// or 64 x 128 (2 x 2 waves).  Consecutive tiles of one round go to the same
+// XCD, so its workgroups share the rows of X through that XCD's L2.  Tiles
+// left over after the whole rounds (fewer than one per workgroup) may be cut
+// along K into parts, one per workgroup, which meet in slots of a caller's
+// buffer (tile_parts.hpp), or, in the calls without one, in Y: by float32
+// atomics into cleared rows, or through tickets.  Without the cut, a shape
+// with a few tiles more than workgroups would take two full rounds
+// (2048 x 8512 x 2048, bfloat16 Y: 105 us, cut 77).
 //
 // Operands reach LDS by direct-to-LDS loads (global_load_lds), with no
 // register staging and one barrier per 64-column stage.  The stage stream
@@ -29,8 +31,10 @@
 //     rows are decoded together (four 64-bit shifts and eight ANDs per 16
 //     codes).
 //   * The group scale is applied in float32, not folded into the bfloat16
-//     operand (folding would cost about 2e-3 relative error).  Instead of a
-//     second set of partial accumulators, each accumulator is kept in units
+//     operand (folding would cost about 2e-3 relative error).  The small tiles
+//     keep a second set of accumulators, one group's products apart from the
+//     scaled total.  The 256 x 256 tile has no registers for that: instead
+//     each of its accumulators is kept in units
 //     of the current group's scale c: when the next group (scale s) starts,
 //     every accumulator block is multiplied by c / s just before its first
 //     MFMA of that group and c becomes s, so the matrix cores keep adding
@@ -723,6 +727,10 @@ hipError_t launch_tgemm_fwd_parts(const uint16_t* X, const uint8_t* codes, const
   FwdPlan p;
   if (have_slots) p = fwd_plan(M, N, K, g);
   if (p.shape == 0 && (!slots || (tickets && !bf16_out))) {
+    // (also where the plan has 256 x 256 tiles and no slots: with rounds before
+    // them, leftover tiles that are not worth a slot's traffic still fill the
+    // chip in parts; 16384 x 8512 x 2048, 128 tiles left after 8 rounds: 518 to
+    // 530 us)
     // 256 x 256 tiles whose parts meet in Y: F whole rounds on P = cus
     // persistent workgroups, then the R = ntiles mod P remaining tiles cut
     // along K into `parts` runs of whole trips (kUnroll stages), one per
