@@ -22,8 +22,11 @@ tm_status tm_rows_sumsq(const float* src, int32_t B, int64_t D, float* dst, floa
 
 /*
  * x = bf16(src / sqrt(sum(part) / K + eps) * norm_w) per batch row (B <= 16,
- * part [B, nparts]), y [B, N] = x . What^T, or += it with accumulate = 1;
- * g = 64, 128 or 256, K <= 4096.  part_out (NULL or [B, ceil(N / 16)]): partial sums of
+ * part [B, nparts]; NULL with nparts = 0: the squares of src are summed by this
+ * call), y [B, N] = x . What^T, or += it with accumulate = 1;
+ * g = 64, 128 or 256, K <= 4096.  With B >= 9 the sums are taken in the order
+ * of tm_tgemv, and the squares, with part NULL, in that of
+ * tm_residual_rmsnorm: the same bits as those two calls.  part_out (NULL or [B, ceil(N / 16)]): partial sums of
  * the squares of y as written.  advance (NULL or a mixer's conv_pos): the
  * ring position moves on by one slot.
  */

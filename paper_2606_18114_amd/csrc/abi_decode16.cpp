@@ -23,9 +23,10 @@ tm_status tm_tgemv_rms16(const float* src, const float* part, int32_t nparts,
                          const uint16_t* scales_f16, int32_t B, int64_t N, int64_t K, int32_t g,
                          float* y, int32_t accumulate, float* part_out, int32_t* advance,
                          tm_stream stream) {
-  if (!src || !part || !norm_w || !codes || !scales_f16 || !y) return TM_EINVAL;
+  if (!src || !norm_w || !codes || !scales_f16 || !y) return TM_EINVAL;
   if (!(eps >= 0.0f) || !std::isfinite(eps) || (accumulate & ~1)) return TM_EINVAL;
-  if (B < 1 || B > 16 || N < 1 || N > (int64_t(1) << 26) || nparts < 1) return TM_ESHAPE;
+  if (B < 1 || B > 16 || N < 1 || N > (int64_t(1) << 26)) return TM_ESHAPE;
+  if (part ? nparts < 1 : nparts != 0) return TM_ESHAPE;
   if (tm_status st = shape_kg(K, g)) return st;
   if (g < 64 || g > 256 || K > tmk::kRms16MaxK) return TM_ESHAPE;
   int64_t xb, wb, cb, sb, yb, pb;
@@ -35,7 +36,7 @@ tm_status tm_tgemv_rms16(const float* src, const float* part, int32_t nparts,
   if (!aligned(src, 16) || !aligned(part, 4) || !aligned(norm_w, 16) || !aligned(codes, 16) ||
       !aligned(scales_f16, 2) || !aligned(y, 4) || !aligned(part_out, 4) || !aligned(advance, 4))
     return TM_EALIGN;
-  const Span ins[5] = {span(src, xb), span(part, pb), span(norm_w, wb), span(codes, cb),
+  const Span ins[5] = {span(src, xb), span(part, part ? pb : 0), span(norm_w, wb), span(codes, cb),
                        span(scales_f16, sb)};
   const Span outs[3] = {span(y, yb), span(part_out, part_out ? B * ((N + 15) / 16) * 4 : 0),
                         span(advance, advance ? 4 : 0)};

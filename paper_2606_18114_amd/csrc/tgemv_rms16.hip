@@ -5,7 +5,9 @@
 //   * the rows' sums of squares arrive as partial sums that the kernel before
 //     wrote on its way (the heads' sums of the mixer, or this kernel's own
 //     part_out: one partial per 16 output rows of the residual it updates), so
-//     no launch reads a row only to normalize it;
+//     no launch reads a row only to normalize it; or, without partial sums,
+//     every workgroup takes them from the rows it reads anyway, one wave per
+//     row;
 //   * every workgroup builds the bfloat16 x of all rows in LDS (coalesced
 //     loads of src, from L2 after the first workgroup of an XCD);
 //   * the convolution ring's position moves on here, after every reader.
@@ -15,41 +17,59 @@
 // The step is bound by the length of each launch's chain of waits, not by its
 // bytes (6.5 MB of codes a layer): the codes are loaded before x, the batch
 // rows are the 16 A rows of v_mfma_f32_16x16x32_bf16 as in tgemv_b16.hip, and
-// the columns are split over 16 waves per workgroup, whose totals meet
-// in LDS in wave order.  (With the MFMA operand normalized straight from
-// global memory, 16 rows at a time in 16-byte pieces, the address unit was the
-// bound: 22 us for 8512 x 2048 and 28 us for 2048 x 4096 at batch 16, against
-// 11.7 and 10.8; the norm and GEMV launches before took 19.9 and 18.2.)
+// the columns are split over 16 waves per workgroup, whose sums meet in LDS.
+// (With the MFMA operand normalized straight from global memory, 16 rows at a
+// time in 16-byte pieces, the address unit was the bound: 22 us for 8512 x
+// 2048 and 28 us for 2048 x 4096 at batch 16, against 12.0 and 11.6; the norm
+// and GEMV launches before took 19.9 and 18.2.)
+//
+// Order of the sums.  A rounding that falls the other way in one activation
+// changes every value after it, so a token of 9 to 16 rows adds in the order
+// of the unfused launches and has their bits: the groups of an output in four
+// contiguous chains (tgemv_b16.hip), the squares of a row without partial sums
+// as residual_rmsnorm takes them (256 chains of every 256th column, then a
+// binary tree).  Below 9 rows the unfused projection is another kernel
+// (tgemv.hip) whose sums this one cannot have; there the chains are 16, one
+// per wave's columns, which need no products in LDS (batch 16 with them: 11.7
+// and 10.8 us).
 #include "common.hpp"
 #include "launchers.hpp"
 #include "mixer_dev.hpp"
 
 namespace tmk {
 
-constexpr int kR16Chunks = 4;  // 64-column chunks whose codes are in flight together
+constexpr int kR16Chunks = 4;  // most 64-column chunks of a wave (K <= 4096, 16 waves)
 constexpr int kR16Quads = 8;   // 4-value pieces of src and w a thread has in flight
 constexpr int kR16Waves = 16;
 
 typedef __attribute__((ext_vector_type(2))) __bf16 r16_bf16x2;
 
 // NB: 16-row blocks of the matrix per workgroup; KMAX: most columns (x takes
-// 32 KMAX bytes of LDS)
+// 32 KMAX bytes of LDS).  part NULL: the rows' squares are summed here.
+// quarters: an output's sum in four chains of groups, else one per wave
 template <int G, int NB, int KMAX, bool ACC>
 __global__ __launch_bounds__(64 * kR16Waves) void tgemv_rms16_kernel(
     const float* __restrict__ src, const float* __restrict__ part, int nparts,
     const float* __restrict__ nw, float eps, const uint8_t* __restrict__ codes,
-    const uint16_t* __restrict__ s16, int B, int N, int K, float* y,
+    const uint16_t* __restrict__ s16, int B, int N, int K, int quarters, float* y,
     float* __restrict__ part_out, int* __restrict__ advance) {
-  static_assert(G % 64 == 0 && kR16Chunks % (G / 64) == 0, "whole groups per round");
+  static_assert(G % 64 == 0 && kR16Chunks % (G / 64) == 0, "whole groups per wave");
   static_assert(64 * kR16Waves >= NB * 256, "a thread per output");
+  static_assert(KMAX <= 64 * kR16Chunks * kR16Waves, "the waves' chunks cover a row");
   constexpr int WAVES = kR16Waves;
   constexpr int kWpg = G / 64;                // chunks per group
-  constexpr int kScales = kR16Chunks / kWpg;  // groups per round
+  constexpr int kGrp = kR16Chunks / kWpg;     // most groups of a wave
   constexpr int kT = 64 * WAVES, kPr = kT / 16;  // threads; threads per batch row (sums)
+  constexpr int kRows = KMAX / 256;  // rows (or pieces of a row) that a thread normalizes
   // x: the 16-byte piece u of row n sits at u ^ (n % 8), so that the operand
-  // reads of 16 rows spread over the banks; the totals reuse its space
-  constexpr int kRed = WAVES * NB * 4 * 64 * 4, kX = 32 * KMAX;
-  __shared__ __attribute__((aligned(16))) uint8_t lds[kX > kRed ? kX : kRed];
+  // reads of 16 rows spread over the banks; what the sums need of LDS reuses
+  // its space (kRb blocks at a time)
+  constexpr int kGroups = KMAX / G, kX = 32 * KMAX;
+  constexpr int kBlk = kGroups * 1024 + 16 * 4 * (kGroups + 4) + 4096;
+  constexpr int kRb = NB * kBlk <= 159 * 1024 ? NB : 2, kRed = kRb * kBlk;
+  constexpr int kSums = WAVES * NB * 1024, kAll = kSums > kRed ? kSums : kRed;
+  static_assert(kAll <= 159 * 1024, "LDS budget");
+  __shared__ __attribute__((aligned(16))) uint8_t lds[kX > kAll ? kX : kAll];
   __shared__ float rs[16];
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
   const int n = lane & 15, kq = lane >> 4;
@@ -57,52 +77,33 @@ __global__ __launch_bounds__(64 * kR16Waves) void tgemv_rms16_kernel(
   const int ngr = K / G, gpw = (ngr + WAVES - 1) / WAVES, g0 = wave * gpw;
   const int gw = ngr - g0 < gpw ? (ngr - g0 > 0 ? ngr - g0 : 0) : gpw;  // groups of this wave
   const int nch = gw * kWpg;
-  const uint32_t* crow[NB];
-  const uint16_t* srow[NB];
-  bool rok[NB];
-#pragma unroll
-  for (int b = 0; b < NB; ++b) {
-    const int row = 16 * (j0 + b) + n;
-    rok[b] = row < N;
-    crow[b] = reinterpret_cast<const uint32_t*>(codes + (int64_t)(rok[b] ? row : 0) * (K / 4));
-    srow[b] = s16 + (int64_t)(rok[b] ? row : 0) * (K / G);
-  }
-  // the output this thread writes: batch row om of row orow
-  const int om = (tid >> 4) & 15, orow = 16 * (j0 + (tid >> 8)) + (tid & 15);
+  // the output this thread writes: batch row om (in the order of the
+  // accumulators' lanes) of row orow
+  const int om = 4 * kq + (wave & 3), orow = 16 * (j0 + (tid >> 8)) + n;
   const bool owner = tid < NB * 256 && om < B && orow < N;
   float base = 0.f;
   if (ACC && owner) base = y[(int64_t)om * N + orow];
 
   uint32_t cw[kR16Chunks][NB];
-  uint16_t sc[NB][kScales];
-  auto load = [&](int i0) {
+  uint16_t sc[NB][kGrp];
 #pragma unroll
-    for (int t = 0; t < kR16Chunks; ++t) {
-      const int i = i0 + t;
-      const int col = g0 * G + 64 * i + 16 * kq;
+  for (int b = 0; b < NB; ++b) {
+    const int row = 16 * (j0 + b) + n;
+    const bool rok = row < N;
+    const uint32_t* crow =
+        reinterpret_cast<const uint32_t*>(codes + (int64_t)(rok ? row : 0) * (K / 4));
+    const uint16_t* srow = s16 + (int64_t)(rok ? row : 0) * (K / G);
 #pragma unroll
-      for (int b = 0; b < NB; ++b) cw[t][b] = 0u;
-      if (i < nch) {
+    for (int t = 0; t < kR16Chunks; ++t)
+      cw[t][b] = rok && t < nch ? crow[g0 * (G / 16) + 4 * t + kq] : 0u;
 #pragma unroll
-        for (int b = 0; b < NB; ++b)
-          if (rok[b]) cw[t][b] = crow[b][col / 16];
-      }
-    }
-#pragma unroll
-    for (int b = 0; b < NB; ++b)
-#pragma unroll
-      for (int r = 0; r < kScales; ++r) {
-        const int gi = i0 / kWpg + r;
-        sc[b][r] = rok[b] && gi < gw ? srow[b][g0 + gi] : (uint16_t)0;
-      }
-  };
-  load(0);
+    for (int r = 0; r < kGrp; ++r) sc[b][r] = rok && r < gw ? srow[g0 + r] : (uint16_t)0;
+  }
 
   // x, rounded to bfloat16 (to nearest even); rows past B are left as they
   // are: an A row only reaches its own output row, which is not written
   const int qpr = K / 4;  // 4-value pieces per row
-  auto put = [&](int row, int q, const u32x4& v, const u32x4& w) {
-    const float r = rs[row];
+  auto put = [&](int row, int q, float r, const u32x4& v, const u32x4& w) {
     uint32_t o[2];
 #pragma unroll
     for (int e = 0; e < 2; ++e) {
@@ -115,35 +116,73 @@ __global__ __launch_bounds__(64 * kR16Waves) void tgemv_rms16_kernel(
     *reinterpret_cast<u32x2*>(lds + (uint32_t)row * (2u * K) + 16u * u + 8u * (q & 1)) =
         u32x2{o[0], o[1]};
   };
-  // the rows' 1 / rms (while loads of src are in flight)
-  auto row_scales = [&]() {
-    const int row = tid / kPr, l = tid % kPr;
-    float s = 0.f;
-    if (row < B)
-      for (int i = l; i < nparts; i += kPr) s += part[(int64_t)row * nparts + i];
+  // 1 / rms of a row from the 64 lanes' sums
+  auto row_scale = [&](float s) {
     s += __uint_as_float(lane_xchg<1>(__float_as_uint(s)));
     s += __uint_as_float(lane_xchg<2>(__float_as_uint(s)));
     s += __uint_as_float(lane_xchg<4>(__float_as_uint(s)));
     s += __uint_as_float(lane_xchg<8>(__float_as_uint(s)));
     s += __uint_as_float(lane_xchg<16>(__float_as_uint(s)));
     s += __uint_as_float(lane_xchg<32>(__float_as_uint(s)));
-    if (l == 0) rs[row] = 1.f / sqrtf(s / (float)K + eps);
-    if (advance && blockIdx.x == 0 && tid == 0) *advance = (*advance + 1) & 3;
+    return 1.f / sqrtf(s / (float)K + eps);
+  };
+  // the rows' 1 / rms (while loads of src are in flight)
+  auto row_scales = [&]() {
+    const int row = tid / kPr, l = tid % kPr;
+    float s = 0.f;
+    if (row < B)
+      for (int i = l; i < nparts; i += kPr) s += part[(int64_t)row * nparts + i];
+    const float r = row_scale(s);
+    if (l == 0) rs[row] = r;
     __syncthreads();
   };
-  if (kT % qpr == 0) {
+  if (advance && blockIdx.x == 0 && tid == 0) *advance = (*advance + 1) & 3;
+  if (part == nullptr) {
+    // wave r takes row r, lane l its pieces l, l + 64, ...: four chains of
+    // every 256th column, then the tree
+    if (wave < B) {
+      const float* row = src + (int64_t)wave * K;
+      constexpr bool kEarly = kRows <= 8;  // registers for the norm weights as well
+      u32x4 v[kRows], w[kEarly ? kRows : 1];
+#pragma unroll
+      for (int j = 0; j < kRows; ++j)
+        if (lane + 64 * j < qpr) {
+          v[j] = ld16(row + 4 * (lane + 64 * j));
+          if constexpr (kEarly) w[j] = ld16(nw + 4 * (lane + 64 * j));
+        }
+      float sq[4] = {0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+      for (int j = 0; j < kRows; ++j)
+        if (lane + 64 * j < qpr) {
+#pragma unroll
+          for (int e = 0; e < 4; ++e) {
+            const float f = __uint_as_float(v[j][e]);
+            sq[e] = __builtin_fmaf(f, f, sq[e]);
+          }
+        }
+      const float r = row_scale((sq[0] + sq[1]) + (sq[2] + sq[3]));
+#pragma unroll
+      for (int j = 0; j < kRows; ++j)
+        if (lane + 64 * j < qpr) {
+          if constexpr (kEarly)
+            put(wave, lane + 64 * j, r, v[j], w[j]);
+          else
+            put(wave, lane + 64 * j, r, v[j], ld16(nw + 4 * (lane + 64 * j)));
+        }
+    }
+  } else if (kT % qpr == 0) {
     // a thread's pieces all lie in the same columns, one load of the norm
-    // weights; at most 16 rows, all in flight at once
+    // weights; at most kRows rows, all in flight at once
     const int step = kT / qpr, row0 = tid / qpr, q = tid % qpr;
     const u32x4 w = ld16(nw + 4 * q);
-    u32x4 v[16];
+    u32x4 v[kRows];
 #pragma unroll
-    for (int j = 0; j < 16; ++j)
+    for (int j = 0; j < kRows; ++j)
       if (row0 + j * step < B) v[j] = ld16(src + (int64_t)(row0 + j * step) * K + 4 * q);
     row_scales();
 #pragma unroll
-    for (int j = 0; j < 16; ++j)
-      if (row0 + j * step < B) put(row0 + j * step, q, v[j], w);
+    for (int j = 0; j < kRows; ++j)
+      if (row0 + j * step < B) put(row0 + j * step, q, rs[row0 + j * step], v[j], w);
   } else {
     // pieces tid, tid + kT, ... in row order, kR16Quads at a time
     const int total = B * qpr, drow = kT / qpr, dcol = kT % qpr;
@@ -174,7 +213,7 @@ __global__ __launch_bounds__(64 * kR16Waves) void tgemv_rms16_kernel(
       if (done > 0) fetch();
 #pragma unroll
       for (int j = 0; j < kR16Quads; ++j)
-        if (at[j] >= 0) put(at[j] >> 16, at[j] & 0xFFFF, v[j], w[j]);
+        if (at[j] >= 0) put(at[j] >> 16, at[j] & 0xFFFF, rs[at[j] >> 16], v[j], w[j]);
     }
   }
   __syncthreads();
@@ -183,48 +222,98 @@ __global__ __launch_bounds__(64 * kR16Waves) void tgemv_rms16_kernel(
     return as_bf16x8(*reinterpret_cast<const u32x4*>(
         lds + (uint32_t)n * (2u * K) + 16u * ((uint32_t)(col / 8) ^ (uint32_t)(n & 7))));
   };
-  float tot[NB][4];
+  f32x4 acc[NB][kGrp];  // each group's products
 #pragma unroll
-  for (int b = 0; b < NB; ++b)
+  for (int t = 0; t < kR16Chunks; ++t) {
+    if (t < nch) {  // uniform
+      const int col = g0 * G + 64 * t + 16 * kq;
+      const bf16x8 a0 = xop(col), a1 = xop(col + 8);
 #pragma unroll
-    for (int e = 0; e < 4; ++e) tot[b][e] = 0.f;
-  for (int i0 = 0; i0 < nch; i0 += kR16Chunks) {
-    if (i0 > 0) load(i0);
-    f32x4 acc[NB];
-#pragma unroll
-    for (int t = 0; t < kR16Chunks; ++t) {
-      if (i0 + t < nch) {  // uniform
-        const int col = g0 * G + 64 * (i0 + t) + 16 * kq;
-        const bf16x8 a0 = xop(col), a1 = xop(col + 8);
-#pragma unroll
-        for (int b = 0; b < NB; ++b) {
-          if (t % kWpg == 0) acc[b] = f32x4{0.f, 0.f, 0.f, 0.f};
-          acc[b] = mfma16(a0, decode_half<0>(cw[t][b]), acc[b]);
-          acc[b] = mfma16(a1, decode_half<1>(cw[t][b]), acc[b]);
-          if (t % kWpg == kWpg - 1) {
-            const float s = h2f(sc[b][t / kWpg]);
-#pragma unroll
-            for (int e = 0; e < 4; ++e) tot[b][e] = __builtin_fmaf(acc[b][e], s, tot[b][e]);
-          }
-        }
+      for (int b = 0; b < NB; ++b) {
+        f32x4& a = acc[b][t / kWpg];
+        if (t % kWpg == 0) a = f32x4{0.f, 0.f, 0.f, 0.f};
+        a = mfma16(a0, decode_half<0>(cw[t][b]), a);
+        a = mfma16(a1, decode_half<1>(cw[t][b]), a);
       }
     }
   }
-  // lane (kq, n) holds batch rows 4 kq + e of weight row n of each block; the
-  // waves meet in LDS
-  __syncthreads();  // x has been read
-  float* red = reinterpret_cast<float*>(lds);
+  // lane (kq, n) holds batch rows 4 kq + e of weight row n of each block.  In
+  // LDS: the chains' sums (chain, block, e, lane)
+  float* sums = reinterpret_cast<float*>(lds);
+  float v = 0.f;
+  if (!quarters) {
+    // a chain is what a wave holds
+    __syncthreads();  // x has been read
 #pragma unroll
-  for (int b = 0; b < NB; ++b)
+    for (int b = 0; b < NB; ++b)
 #pragma unroll
-    for (int e = 0; e < 4; ++e) red[((wave * NB + b) * 4 + e) * 64 + lane] = tot[b][e];
-  __syncthreads();
+      for (int e = 0; e < 4; ++e) {
+        float run = 0.f;
+#pragma unroll
+        for (int r = 0; r < kGrp; ++r)
+          if (r < gw) run = __builtin_fmaf(acc[b][r][e], h2f(sc[b][r]), run);
+        sums[((wave * NB + b) * 4 + e) * 64 + lane] = run;
+      }
+    __syncthreads();
+    if (tid < NB * 256) {
+      float sum = 0.f;
+#pragma unroll
+      for (int w = 0; w < WAVES; ++w) sum += sums[w * (NB * 256) + (tid >> 6) * 64 + lane];
+      v = 0.5f * sum;  // the codes decode to 2q
+    }
+  } else {
+    // a chain is a quarter of the row's groups, from several waves: the groups'
+    // products (group, block, e, lane) and scales (block, n, group) go to LDS,
+    // and wave w takes the chains w, w + 16, ... (4 (4 b + e) + quarter)
+    constexpr int kLd = kGroups + 4;
+    float* red = sums + 4 * kRb * 256;
+    float* scl = red + kGroups * kRb * 256;
+    const int len = (ngr + 3) / 4;
+#pragma unroll
+    for (int b0 = 0; b0 < NB; b0 += kRb) {
+      __syncthreads();  // x, or the blocks before, have been read
+#pragma unroll
+      for (int b = b0; b < b0 + kRb && b < NB; ++b)
+#pragma unroll
+        for (int r = 0; r < kGrp; ++r)
+          if (r < gw) {
+            const int at = (g0 + r) * kRb + (b - b0);
+#pragma unroll
+            for (int e = 0; e < 4; ++e) red[(at * 4 + e) * 64 + lane] = acc[b][r][e];
+            if (kq == 0) scl[((b - b0) * 16 + n) * kLd + g0 + r] = h2f(sc[b][r]);
+          }
+      __syncthreads();
+      float run[kRb];
+#pragma unroll
+      for (int i = 0; i < kRb; ++i) run[i] = 0.f;
+#pragma unroll 4
+      for (int g = 0; g < len; ++g) {
+#pragma unroll
+        for (int i = 0; i < kRb; ++i) {
+          const int c = wave + 16 * i, be = c >> 2, at = (c & 3) * len + g;
+          const bool in = at < ngr && b0 + (be >> 2) < NB;
+          const float f = red[((in ? at : 0) * (kRb * 4) + be) * 64 + lane];
+          const float c1 = scl[((be >> 2) * 16 + n) * kLd + (in ? at : 0)];
+          run[i] = in ? __builtin_fmaf(f, c1, run[i]) : run[i];
+        }
+      }
+#pragma unroll
+      for (int i = 0; i < kRb; ++i) {
+        const int c = wave + 16 * i;
+        sums[((c & 3) * (kRb * 4) + (c >> 2)) * 64 + lane] = run[i];
+      }
+      __syncthreads();
+      const int be = (tid >> 6) - 4 * b0;  // (block, e) of this thread's output
+      if (be >= 0 && be < 4 * kRb) {
+        float sum = 0.f;
+#pragma unroll
+        for (int c = 0; c < 4; ++c) sum += sums[(c * (kRb * 4) + be) * 64 + lane];
+        v = 0.5f * sum;
+      }
+    }
+  }
   if (tid < NB * 256) {
-    const float* p = red + ((tid >> 8) * 4 + (om & 3)) * 64 + (om >> 2) * 16 + (tid & 15);
-    float sum = 0.f;
-#pragma unroll
-    for (int w = 0; w < WAVES; ++w) sum += p[w * NB * 256];
-    const float v = ACC ? base + 0.5f * sum : 0.5f * sum;  // the codes decode to 2q
+    if constexpr (ACC) v = __fadd_rn(base, v);
     if (owner) y[(int64_t)om * N + orow] = v;
     if (part_out) {
       // the block's 16 rows of this batch row
@@ -234,7 +323,7 @@ __global__ __launch_bounds__(64 * kR16Waves) void tgemv_rms16_kernel(
       sq += __uint_as_float(lane_xchg<4>(__float_as_uint(sq)));
       sq += __uint_as_float(lane_xchg<8>(__float_as_uint(sq)));
       const int blk = j0 + (tid >> 8), nblk = (N + 15) / 16;
-      if ((tid & 15) == 0 && om < B && blk < nblk) part_out[(int64_t)om * nblk + blk] = sq;
+      if (n == 0 && om < B && blk < nblk) part_out[(int64_t)om * nblk + blk] = sq;
     }
   }
 }
@@ -276,10 +365,11 @@ static hipError_t launch_r16(const float* src, const float* part, int nparts, co
                              int K, float* y, float* part_out, int* advance,
                              hipStream_t stream) {
   const int nblk = (N + 15) / 16, cus = current_cu_count();
+  const int quarters = tgemv_b16_takes(B, G) ? 1 : 0;
 #define TM_R16(NB_)                                                                          \
   hipLaunchKernelGGL((tgemv_rms16_kernel<G, NB_, KMAX, ACC>), dim3((nblk + NB_ - 1) / NB_),  \
                      dim3(64 * kR16Waves), 0, stream, src, part, nparts, nw, eps, codes, s16, \
-                     B, N, K, y, part_out, advance)
+                     B, N, K, quarters, y, part_out, advance)
   if (nblk <= cus)
     TM_R16(1);
   else if (nblk <= 2 * cus)

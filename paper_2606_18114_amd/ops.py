@@ -681,13 +681,15 @@ def rows_sumsq(src: torch.Tensor, part: torch.Tensor, dst: Optional[torch.Tensor
 RMS16_MAX_K = 4096  # columns tm_tgemv_rms16 takes
 
 
-def tgemv_rms16(src: torch.Tensor, part: torch.Tensor, codes: torch.Tensor,
+def tgemv_rms16(src: torch.Tensor, part: Optional[torch.Tensor], codes: torch.Tensor,
                 scales_f16: torch.Tensor, g: int, norm_w: torch.Tensor, eps: float,
                 y: torch.Tensor, accumulate: bool = False,
                 part_out: Optional[torch.Tensor] = None,
                 advance: Optional[torch.Tensor] = None) -> torch.Tensor:
     """tgemv_rms for up to 16 rows at g = 64, 128 or 256, the rows' sums of
-    squares given as partial sums (part float32 [B, P]).  part_out (optional,
+    squares given as partial sums (part float32 [B, P]) or, with None, summed
+    by the call.  With 9 rows or more the results have the bits of
+    ``residual_rmsnorm`` (part None) and ``tgemv``.  part_out (optional,
     float32 [B, ceil(N/16)]) receives those of y as written; advance
     (optional): a mixer's conv_pos, moved on by one slot."""
     _need(codes, "codes", _U8, 2)
@@ -696,15 +698,17 @@ def tgemv_rms16(src: torch.Tensor, part: torch.Tensor, codes: torch.Tensor,
     _need(scales_f16, "scales_f16", _F16, 2)
     _shape(codes, "codes", (N, K // 4), src.device)
     _shape(scales_f16, "scales_f16", (N, _groups(K, g)), src.device)
-    _need(part, "part", _F32, 2)
-    _shape(part, "part", (B, part.shape[1]), src.device)
+    if part is not None:
+        _need(part, "part", _F32, 2)
+        _shape(part, "part", (B, part.shape[1]), src.device)
     if part_out is not None:
         _need(part_out, "part_out", _F32, 2)
         _shape(part_out, "part_out", (B, (N + 15) // 16), src.device)
     if advance is not None:
         _need(advance, "advance", (torch.int32,), 1)
         _shape(advance, "advance", (1,), src.device)
-    st = lib().tm_tgemv_rms16(_ptr(src), _ptr(part), part.shape[1], _ptr(norm_w), eps,
+    st = lib().tm_tgemv_rms16(_ptr(src), _ptr(part), 0 if part is None else part.shape[1],
+                              _ptr(norm_w), eps,
                               _ptr(codes), _ptr(scales_f16), B, N, K, g, _ptr(y),
                               int(bool(accumulate)), _ptr(part_out), _ptr(advance), _stream())
     _check("tm_tgemv_rms16", st)

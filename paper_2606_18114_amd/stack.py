@@ -211,7 +211,9 @@ class Mamba2Decoder:
 
     or, for batches the fused form does not take (no kept layers, g 64, 128 or
     256), its three launches with the rows' sums of squares passed from one to
-    the next: tm_tgemv_rms16, tm_mixer_gate_part, tm_tgemv_rms16;
+    the next: tm_tgemv_rms16, tm_mixer_gate_part, tm_tgemv_rms16 (9 to 16 rows:
+    the bits of the unfused form; 5 to 8: the unfused form's projections round
+    their sums differently);
 
     or the whole stack in one launch (``tm_mamba2_decode_token``: the three
     phases of every block separated by grid barriers instead of launches;
@@ -332,9 +334,10 @@ class Mamba2Decoder:
         self.stack_ws = (ops.mamba2_decode_workspace(d_model, nheads, dev, batch)
                          if self.stack else None)
         if self.fused16:
-            self.part_emb = torch.empty((batch, 1), dtype=torch.float32, device=dev)
-            self.part_res = torch.empty((batch, (d_model + 15) // 16), dtype=torch.float32,
-                                        device=dev)
+            if batch < 9:
+                self.part_emb = torch.empty((batch, 1), dtype=torch.float32, device=dev)
+                self.part_res = torch.empty((batch, (d_model + 15) // 16), dtype=torch.float32,
+                                            device=dev)
             self.part_gate = torch.empty((batch, nheads), dtype=torch.float32, device=dev)
         self.graph = None
 
@@ -385,10 +388,18 @@ class Mamba2Decoder:
         self._proj(lay, "out", self.m, self.y)
 
     def _token16(self) -> None:
-        """Every layer of a token on the batched fused launches: each one
-        leaves the sums of squares the next one normalizes its rows with."""
-        part = self.part_emb
-        ops.rows_sumsq(self.emb, part, dst=self.residual)
+        """Every layer of a token on the batched fused launches.  Up to 8 rows
+        each one leaves the sums of squares the next one normalizes its rows
+        with; from 9 rows on in_proj sums the residual's squares by itself, in
+        the order of the unfused form, whose bits a token then has (a rounding
+        that falls the other way in one block changes the outputs of 48 by
+        0.6%; 48 blocks at 16 rows: 1753 us, 1730 with the sums passed on)."""
+        part = out = None
+        if self.B < 9:
+            part, out = self.part_emb, self.part_res
+            ops.rows_sumsq(self.emb, part, dst=self.residual)
+        else:
+            self.residual.copy_(self.emb)
         for lay in self.layers:
             mp, (_, ic, isc), (_, oc, osc) = lay["mixer"], lay["in"], lay["out"]
             ops.tgemv_rms16(self.residual, part, ic[0], isc[0], self.g, lay["pre"], self.eps,
@@ -396,7 +407,7 @@ class Mamba2Decoder:
             ops.mixer_gate_part(self.zx[0], lay["conv"], lay["pos"], lay["ssm"], mp["conv_w"],
                                 mp["conv_b"], mp["dt_bias"], mp["A_log"], mp["D"], self.gated,
                                 self.part_gate)
-            part = self.part_res
+            part = out
             ops.tgemv_rms16(self.gated, self.part_gate, oc[0], osc[0], self.g, mp["norm_w"],
                             self.eps, self.residual, accumulate=True, part_out=part,
                             advance=lay["pos"])

@@ -61,8 +61,35 @@ def test_projection(B, N, K, g, accumulate):
     assert torch.allclose(part_out.double(), sq.view(B, -1, 16).sum(2), rtol=2e-6)
 
 
+def _bits(t):
+    return t.contiguous().view(torch.uint8)
+
+
+# one in nine rows and all sixteen, fewer groups than waves and several per
+# wave, columns that are no multiple of 256, rows that end inside a block
+@pytest.mark.parametrize("B,N,K,g", [(9, 17, 64, 64), (16, 8512, 2048, 128), (16, 2048, 4096, 64),
+                                     (12, 8500, 3904, 64), (16, 12400, 4096, 64),
+                                     (11, 530, 1280, 256), (10, 8200, 1088, 64),
+                                     (13, 6170, 2176, 128)])
+def test_projection_has_the_bits_of_the_unfused_launches(B, N, K, g):
+    print(f"[decode16] bits B={B} N={N} K={K} g={g}", flush=True)
+    gen = torch.Generator(device="cuda").manual_seed(B + N)
+    codes, s16, _ = _packed(gen, N, K, g)
+    src = torch.randn((B, K), generator=gen, device="cuda")
+    nw = 1 + 0.1 * torch.randn(K, generator=gen, device="cuda")
+    y0 = torch.randn((B, N), generator=gen, device="cuda")
+    x = torch.empty((1, B, K), dtype=torch.bfloat16, device="cuda")
+    ops.residual_rmsnorm(src.clone(), None, nw, 1e-5, x=x[0])
+    ref = ops.tgemv(x, codes[None], s16[None], g)[0]
+    for accumulate in (False, True):
+        y = y0.clone()
+        ops.tgemv_rms16(src, None, codes, s16, g, nw, 1e-5, y, accumulate=accumulate)
+        assert torch.equal(_bits(y), _bits(y0 + ref if accumulate else ref))
+
+
 @pytest.mark.parametrize("B,d_model,heads,g", [(5, 256, 8, 64), (16, 512, 16, 128),
-                                               (12, 768, 24, 256), (8, 2048, 64, 128)])
+                                               (12, 768, 24, 256), (8, 2048, 64, 128),
+                                               (9, 1024, 64, 64), (16, 2048, 64, 128)])
 def test_token_matches_the_unfused_decode(B, d_model, heads, g):
     print(f"[decode16] token B={B} d_model={d_model} heads={heads} g={g}", flush=True)
     L, di = 3, 64 * heads
@@ -92,6 +119,10 @@ def test_token_matches_the_unfused_decode(B, d_model, heads, g):
             a.capture()
         xa = (a.replay() if step >= 2 else a.token()).float()
         xb = b.token().float()
+        if B >= 9:  # the same sums in the same order
+            assert torch.equal(_bits(xa), _bits(xb))
+            for k in ("ssm_state", "conv_state"):
+                assert torch.equal(_bits(a.arena[k]), _bits(b.arena[k]))
         # each of the 2 L activations handed on may round to the other
         # bfloat16 neighbour: 2^-9 each, at most as independent errors
         assert float((xa - xb).norm() / xb.norm()) <= 2.0 ** -8 * (2 * L) ** 0.5
