@@ -305,21 +305,30 @@ __global__ __launch_bounds__(256) void tgemv_b16_few_kernel(const uint16_t* __re
 
 // Past four blocks per CU x goes through LDS, else each block is a workgroup of
 // its own (8 matrices of 1024 x 2048, 512 blocks: 64 workgroups of the first
-// form leave the chip idle).  Blocks per wave: as many, up to four, as leave
-// two rounds of workgroups on the chip (each copies x once for all its blocks).
+// form leave the chip idle).  At g = 64 a lane's codes come in 4-byte words,
+// and where the 16 waves of K > 2048 take a CU each the first form pays only
+// from six or seven blocks per CU on (4 matrices of 4400 x 4096, 1100 blocks: 48
+// us at batch 16, 38 as workgroups of their own, 46 and 32 at batch 9; of 6400
+// rows, 1600 blocks: 50 and 55, 48 and 43; at g = 128, batch 16: 27 and 34, 29
+// and 46).  Blocks per wave: as many, up to four, as
+// leave two rounds of workgroups on the chip (each copies x once for all its
+// blocks).
 template <int G>
 static hipError_t launch_b16_g(const uint16_t* x, const uint8_t* codes, const uint16_t* s16,
                                int count, int B, int64_t N, int64_t K, float* y,
                                hipStream_t stream) {
-  if (N > 0x7FFFFF00 || K > 0x7FFFFFFF) return hipErrorInvalidValue;
+  if (N > 0x7FFFFFFF || K > 0x7FFFFFFF) return hipErrorInvalidValue;
   const bool wide = K > 2048;
   const int64_t nblk = (N + 15) / 16, W = wide ? 16 : 8;
   const int64_t waves = (int64_t)current_cu_count() * 16;  // on the chip at once
-  if (4 * count * nblk <= waves) {
+  const int per_cu = G == 64 && wide ? (B < 13 ? 7 : 6) : 4;
+  if (16 * count * nblk <= per_cu * waves) {
     hipLaunchKernelGGL((tgemv_b16_few_kernel<G>), dim3((unsigned)(count * nblk)), dim3(256), 0,
                        stream, x, codes, s16, B, (int)N, (int)K, (int)nblk, y);
     return hipGetLastError();
   }
+  // (16 W bpw rows of a workgroup divide 2^31 where N is near it, so the row
+  // numbers of the last one fit an int)
   int64_t bpw = count * nblk / (2 * waves);
   bpw = bpw < 1 ? 1 : (bpw > 4 ? 4 : bpw);
   const int64_t wgs = (nblk + W * bpw - 1) / (W * bpw), grid = count * wgs;

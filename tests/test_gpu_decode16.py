@@ -134,11 +134,13 @@ def test_token_matches_the_unfused_decode(B, d_model, heads, g):
 
 # (matrices, B, N, K, g): past four 16-row blocks per CU x is copied to LDS;
 # one, two and four blocks per wave, K below, at and past a window of columns,
-# rounds with one group and with sixteen, ragged rows and matrices
+# rounds with one group and with sixteen, ragged rows and matrices; g = 64 at K
+# past 2048 on both sides of its own line
 @pytest.mark.parametrize("count,B,N,K,g", [(3, 9, 5500, 4160, 64), (2, 16, 8500, 4608, 512),
                                            (1, 12, 16500, 64, 64), (1, 16, 262149, 64, 64),
                                            (1, 10, 524300, 128, 128), (4, 16, 4300, 2048, 256),
-                                           (4, 11, 4300, 2304, 128), (1, 16, 1000, 8192, 256)])
+                                           (4, 11, 4300, 2304, 128), (1, 16, 1000, 8192, 256),
+                                           (6, 9, 5500, 4160, 64), (3, 12, 9000, 4480, 128)])
 def test_batched_gemv(count, B, N, K, g):
     print(f"[decode16] gemv {count} x B={B} N={N} K={K} g={g}", flush=True)
     gen = torch.Generator(device="cuda").manual_seed(N + K)
