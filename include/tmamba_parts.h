@@ -19,14 +19,19 @@
 extern "C" {
 #endif
 
+/* the larger of the two tm_tgemm_fwd_scratch */
 int64_t tm_tgemm_fwd_slots(int64_t M, int64_t N, int64_t K, int32_t g);
+int64_t tm_tgemm_fwd_scratch(int64_t M, int64_t N, int64_t K, int32_t g, int32_t y_bf16);
 int64_t tm_tgemm_bwd_dx_slots(int64_t M, int64_t N, int64_t K, int32_t exact);
 int64_t tm_tgemm_bwd_dw_slots(int64_t M, int64_t N, int64_t K);
 
 /*
  * Y = X . What^T in float32 (y_bf16 = 0) or rounded once to bfloat16
  * (y_bf16 = 1), on the tile shape and cut that suit the sizes.  workspace:
- * NULL, or that of tm_tgemm_fwd_ws (float32 only).
+ * NULL, or that of tm_tgemm_fwd_ws (float32 only).  slots (at least
+ * tm_tgemm_fwd_scratch bytes): the parts' slots, or, where two parts meet in Y,
+ * the words they take turns with if there is no workspace.  With slots, or
+ * where none are needed, two calls give the same bits.
  */
 tm_status tm_tgemm_fwd_parts(const uint16_t* X, const uint8_t* codes, const float* scales,
                              int64_t M, int64_t N, int64_t K, int32_t g, void* Y, int32_t y_bf16,

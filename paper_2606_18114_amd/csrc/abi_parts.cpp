@@ -40,8 +40,14 @@ int64_t tm_tgemm_bwd_dw_slots(int64_t M, int64_t N, int64_t K) {
 }
 
 int64_t tm_tgemm_fwd_slots(int64_t M, int64_t N, int64_t K, int32_t g) {
-  if (!sizes_ok(M, N, K) || shape_kg(K, g) != TM_OK) return -1;
-  return tmk::fwd_slot_bytes(M, N, K, g);
+  const int64_t f32 = tm_tgemm_fwd_scratch(M, N, K, g, 0);
+  const int64_t b16 = tm_tgemm_fwd_scratch(M, N, K, g, 1);
+  return f32 > b16 ? f32 : b16;
+}
+
+int64_t tm_tgemm_fwd_scratch(int64_t M, int64_t N, int64_t K, int32_t g, int32_t y_bf16) {
+  if (!sizes_ok(M, N, K) || shape_kg(K, g) != TM_OK || (y_bf16 & ~1)) return -1;
+  return tmk::fwd_scratch_bytes(M, N, K, g, y_bf16 != 0);
 }
 
 tm_status tm_tgemm_fwd_parts(const uint16_t* X, const uint8_t* codes, const float* scales,
@@ -52,7 +58,7 @@ tm_status tm_tgemm_fwd_parts(const uint16_t* X, const uint8_t* codes, const floa
   const int es = y_bf16 ? 2 : 4;
   if (tm_status st = fwd_checked(X, codes, scales, M, N, K, g, Y, es, workspace, workspace_bytes))
     return st;
-  const int64_t need = tm_tgemm_fwd_slots(M, N, K, g);
+  const int64_t need = tm_tgemm_fwd_scratch(M, N, K, g, y_bf16);
   const Span ops[5] = {span(X, M * K * 2), span(codes, N * (K / 4)), span(scales, N * (K / g) * 4),
                        span(Y, M * N * es), span(workspace, workspace ? kFwdTicketBytes : 0)};
   if (tm_status st = slots_checked(slots, slots_bytes, need, ops, 5)) return st;

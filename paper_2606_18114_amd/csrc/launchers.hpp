@@ -66,12 +66,12 @@ hipError_t launch_tgemm_bwd_dw(const uint16_t* dY, const uint16_t* X, int64_t M,
 // slots NULL, or the *_slot_bytes of the shape (0: no tile is cut); dX also
 // rounded once to bfloat16 (then slots are needed where a tile is cut), and
 // dY in float32 (f32_in; its bfloat16 rounding is written to dYb).
-int64_t fwd_slot_bytes(int64_t M, int64_t N, int64_t K, int g);
-// have_slots: slots of fwd_slot_bytes (NULL where that is 0) are given and
-// the plan may use every tile shape; tickets may be NULL
+int64_t fwd_scratch_bytes(int64_t M, int64_t N, int64_t K, int g, bool bf16_out);
+// have_scratch: scratch of fwd_scratch_bytes (NULL where that is 0), slots or
+// tickets, is given and the plan may use every tile shape; tickets may be NULL
 hipError_t launch_tgemm_fwd_parts(const uint16_t* X, const uint8_t* codes, const float* scales,
                                   int64_t M, int64_t N, int64_t K, int g, void* Y, bool bf16_out,
-                                  uint32_t* tickets, float* slots, bool have_slots,
+                                  uint32_t* tickets, void* scratch, bool have_scratch,
                                   hipStream_t stream);
 int64_t bwd_dx_slot_bytes(int64_t M, int64_t N, int64_t K);
 int64_t bwd_dx_f16_slot_bytes(int64_t M, int64_t N, int64_t K);

@@ -8,8 +8,9 @@
 // XCD, so its workgroups share the rows of X through that XCD's L2.  Tiles
 // left over after the whole rounds (fewer than one per workgroup) may be cut
 // along K into parts, one per workgroup, which meet in slots of a caller's
-// buffer (tile_parts.hpp), or, in the calls without one, in Y: by float32
-// atomics into cleared rows, or through tickets.  Without the cut, a shape
+// buffer (tile_parts.hpp), or in Y: two parts through tickets, or, in the calls
+// without a buffer, any number by float32 atomics into cleared rows.  Without
+// the cut, a shape
 // with a few tiles more than workgroups would take two full rounds
 // (2048 x 8512 x 2048, bfloat16 Y: 105 us, cut 77).
 //
@@ -666,119 +667,143 @@ struct FwdShape {
 constexpr FwdShape kFwdShapes[3] = {{256, 256, 1, 1.75, 0.95, 0.10},
                                     {128, 128, 2, 0.98, 0.55, 0.025},
                                     {64, 128, 3, 0.92, 0.38, 0.0125}};
-constexpr double kFwdLaunchUs = 5.0, kFwdTileUs = 1.0;
+constexpr double kFwdLaunchUs = 5.0, kFwdTileUs = 1.0, kFwdTicketUs = 0.05;
+
+// How the parts of a cut tile meet
+enum class FwdMeet { kWhole, kSlots, kTickets, kAtomics };
 
 struct FwdPlan {
   int shape = 0;
   int64_t grid = 0, full = 0, rem = 0;
   int parts = 1;
-  int64_t slot_bytes() const {
-    return parts > 1 ? rem * parts * kFwdShapes[shape].bm * kFwdShapes[shape].bn * 4 : 0;
+  FwdMeet meet = FwdMeet::kWhole;
+  int64_t scratch_bytes() const {
+    if (meet == FwdMeet::kTickets) return 8 * (int64_t)kFwdMaxTicketTiles;
+    if (meet != FwdMeet::kSlots) return 0;
+    return rem * parts * kFwdShapes[shape].bm * kFwdShapes[shape].bn * 4;
   }
 };
 
-// Tile shape and cut of a forward with slots: least estimated time (whole
-// rounds, the longest run of the leftover tiles, the parts' traffic and
-// reduction).  Large outputs run on 256 x 256 tiles, which read their operands
+static int fwd_unroll(int64_t K, int g) {
+  const int ss = K % 256 == 0 ? 4 : 1;
+  return ss > g / kFwdBK ? ss : g / kFwdBK;
+}
+
+// Tile shape and cut of a forward that has scratch: least estimated time
+// (whole rounds, the longest run of the leftover tiles, what their parts cost
+// to join).  Large outputs run on 256 x 256 tiles, which read their operands
 // least often (16384 x 8512 x 2048: 520 us, 128 x 128 tiles 570); an output of
 // a few hundred of those leaves CUs idle in its last or only round, where the
 // smaller tiles fill the chip and the workgroups of a CU hide each other's
-// waits (4096 x 2048 x 4096: 256 x 256 tiles cut in two 92 us, 128 x 128
-// tiles 64; 300 x 8512 x 2048: 55 and, on 64 x 128 tiles, 21).
-static FwdPlan fwd_plan(int64_t M, int64_t N, int64_t K, int g) {
+// waits (4096 x 2048 x 4096: 256 x 256 tiles cut in two 79 us, 128 x 128
+// tiles 65; 300 x 8512 x 2048: 38 and, on 64 x 128 tiles, 20).  Tickets join
+// two parts of a 256 x 256 tile with float32 results; they pay after whole
+// rounds, where the two parts of a tile do not end together (with the same
+// stores in Y on all sides, 8192 x 8512 x 2048, 64 tiles left: whole 270, slots
+// 264, tickets 260; 20480 x 2048 x 4096, 128 left: 314, 301, 289; 16384 x 8512
+// x 2048, 128 left: 515, 521, 513; with no round before, 4096 x 2048 x 4096:
+// slots 79, tickets 85).
+static FwdPlan fwd_plan(int64_t M, int64_t N, int64_t K, int g, bool bf16_out) {
   const int cus = current_cu_count();
-  const bool wide = K % 256 == 0;
-  const int unroll = (wide ? 4 : 1) > g / kFwdBK ? (wide ? 4 : 1) : g / kFwdBK;
+  const int unroll = fwd_unroll(K, g);
   const int64_t trips = K / kFwdBK / unroll;
   FwdPlan best;
   double best_t = 0;
   for (int i = 0; i < 3; ++i) {
     const FwdShape& c = kFwdShapes[i];
+    const FwdShape& s = c;
     const int64_t tiles = ((M + c.bm - 1) / c.bm) * ((N + c.bn - 1) / c.bn);
     if (tiles > 0x7FFFFFFF) continue;  // 32-bit tile numbers
-    const int64_t P = (int64_t)cus * c.per_cu;
+    const int64_t P = (int64_t)cus * s.per_cu;
     const int64_t F = tiles / P, R = tiles % P;
     const int64_t most = R > 0 ? (P / R < trips ? P / R : trips) : 1;
     for (int64_t k = 1; k <= most; ++k) {
       const int64_t run = R > 0 ? (trips + k - 1) / k : 0;
       if (k > 1 && run == (trips + k - 2) / (k - 1)) continue;  // no shorter than k - 1 parts
       const double load = (double)(R * k) / (double)P;
-      double t = (double)(F * trips * unroll) * c.full_us +
-                 (double)(run * unroll) * (c.alone_us + (c.full_us - c.alone_us) * load) +
-                 (double)(F + (R > 0)) * kFwdTileUs;
-      // (a slot's blocks past M are neither written nor read)
-      if (k > 1)
-        t += kFwdLaunchUs +
-             (double)(R * k) * c.slot_us * (M < c.bm ? (double)((M + 31) / 32 * 32) / c.bm : 1.0);
-      if (best.grid == 0 || t < best_t) {
-        best_t = t;
+      const double t = (double)(F * trips * unroll) * s.full_us +
+                       (double)(run * unroll) * (s.alone_us + (s.full_us - s.alone_us) * load) +
+                       (double)(F + (R > 0)) * kFwdTileUs;
+      auto offer = [&](FwdMeet meet, double join_us) {
+        if (best.grid != 0 && t + join_us >= best_t) return;
+        best_t = t + join_us;
         best.shape = i;
         best.full = F;
         best.rem = R;
         best.parts = (int)k;
+        best.meet = meet;
         best.grid = F > 0 ? P : R * k;
+      };
+      if (k == 1) {
+        offer(FwdMeet::kWhole, 0.0);
+        continue;
       }
+      // (a slot's blocks past M are neither written nor read)
+      offer(FwdMeet::kSlots,
+            kFwdLaunchUs + (double)(R * k) * c.slot_us *
+                               (M < c.bm ? (double)((M + 31) / 32 * 32) / c.bm : 1.0));
+      if (k == 2 && i == 0 && F > 0 && !bf16_out && R >= kFwdMinTicketTiles &&
+          R <= kFwdMaxTicketTiles)
+        offer(FwdMeet::kTickets, (double)R * kFwdTicketUs);
     }
   }
   return best;
 }
 
-int64_t fwd_slot_bytes(int64_t M, int64_t N, int64_t K, int g) {
-  return fwd_plan(M, N, K, g).slot_bytes();
+// Without scratch: 256 x 256 tiles, F whole rounds on P = cus persistent
+// workgroups, then the R = tiles mod P remaining ones cut along K into `parts`
+// runs of whole trips, one per workgroup, when that leaves at least two parts
+// per tile; otherwise whole to the first R workgroups.  Two parts meet through
+// tickets if given (with few cut tiles the atomics cost little and the second
+// part's wait for the first, which then finishes at about the same time, would
+// show), else the parts add up by atomics in cleared rows of Y; bfloat16
+// results are not summed in parts.
+static FwdPlan fwd_plan_in_place(int64_t M, int64_t N, int64_t K, int g, bool bf16_out,
+                                 bool tickets) {
+  FwdPlan p;
+  const int64_t tiles = ((M + 255) / 256) * ((N + 255) / 256);
+  const int64_t P = current_cu_count(), trips = K / kFwdBK / fwd_unroll(K, g);
+  p.full = tiles / P;
+  p.rem = tiles % P;
+  p.grid = P;
+  int64_t parts = p.rem > 0 ? P / p.rem : 1;
+  if (parts > trips) parts = trips;
+  if (parts < 2 || bf16_out) return p;
+  p.parts = (int)parts;
+  p.meet = tickets && parts == 2 && p.rem >= kFwdMinTicketTiles && p.rem <= kFwdMaxTicketTiles
+               ? FwdMeet::kTickets
+               : FwdMeet::kAtomics;
+  return p;
+}
+
+int64_t fwd_scratch_bytes(int64_t M, int64_t N, int64_t K, int g, bool bf16_out) {
+  return fwd_plan(M, N, K, g, bf16_out).scratch_bytes();
 }
 
 hipError_t launch_tgemm_fwd_parts(const uint16_t* X, const uint8_t* codes, const float* scales,
                                   int64_t M, int64_t N, int64_t K, int g, void* Y, bool bf16_out,
-                                  uint32_t* tickets, float* slots, bool have_slots,
+                                  uint32_t* tickets, void* scratch, bool have_scratch,
                                   hipStream_t stream) {
   const bool wide = K % 256 == 0;  // code stages of four X stages
-  FwdPlan p;
-  if (have_slots) p = fwd_plan(M, N, K, g);
-  if (p.shape == 0 && (!slots || (tickets && !bf16_out))) {
-    // (also where the plan has 256 x 256 tiles and no slots: with rounds before
-    // them, leftover tiles that are not worth a slot's traffic still fill the
-    // chip in parts; 16384 x 8512 x 2048, 128 tiles left after 8 rounds: 518 to
-    // 530 us)
-    // 256 x 256 tiles whose parts meet in Y: F whole rounds on P = cus
-    // persistent workgroups, then the R = ntiles mod P remaining tiles cut
-    // along K into `parts` runs of whole trips (kUnroll stages), one per
-    // workgroup, when that leaves at least two parts per tile; otherwise the
-    // remaining tiles go whole to the first R workgroups.
-    const int64_t tn = (N + 255) / 256, ntiles = ((M + 255) / 256) * tn;
-    const int64_t P = current_cu_count();
-    const int unroll = (wide ? 4 : 1) > g / kFwdBK ? (wide ? 4 : 1) : g / kFwdBK;
-    const int64_t trips = K / kFwdBK / unroll;
-    FwdPlan q;
-    q.full = ntiles / P;
-    q.rem = ntiles % P;
-    int64_t parts = q.rem > 0 ? P / q.rem : 1;
-    if (parts > trips) parts = trips;
-    if (parts < 1 || bf16_out) parts = 1;  // bfloat16 results are not summed in parts
-    q.parts = (int)parts;
-    q.grid = P;
-    // two parts per cut tile and tickets given: the first part writes, the
-    // second adds (Y is not cleared; the tickets are, by a fill kernel).  With
-    // few cut tiles the atomics cost little and the second part's wait for the
-    // first (which then finishes at about the same time) would show: atomics.
-    if (parts != 2 || q.rem < kFwdMinTicketTiles || q.rem > kFwdMaxTicketTiles) tickets = nullptr;
-    if (tickets || !slots) {
-      p = q;
-      slots = nullptr;
-    }
-    if (tickets) {
-      hipError_t e = launch_fill_zero_f32(reinterpret_cast<float*>(tickets), 2 * q.rem, stream);
-      if (e != hipSuccess) return e;
-    } else if (!slots && p.parts > 1) {
-      // the cut tiles accumulate atomically: clear their rows of Y first (a
-      // fill kernel, not a memset node, so the call can be captured)
-      const int64_t r0 = p.full * P / tn * 256;
-      hipError_t e = launch_fill_zero_f32(static_cast<float*>(Y) + r0 * N, (M - r0) * N, stream);
-      if (e != hipSuccess) return e;
-    }
-  } else {
+  const FwdPlan p = have_scratch ? fwd_plan(M, N, K, g, bf16_out)
+                                 : fwd_plan_in_place(M, N, K, g, bf16_out, tickets != nullptr);
+  float* slots = p.meet == FwdMeet::kSlots ? static_cast<float*>(scratch) : nullptr;
+  if (p.meet != FwdMeet::kTickets)
     tickets = nullptr;
+  else if (tickets == nullptr)
+    tickets = static_cast<uint32_t*>(scratch);
+  if (p.meet == FwdMeet::kTickets) {
+    // Y is not cleared; the tickets are (by a fill kernel, not a memset node, so
+    // the call can be captured)
+    const hipError_t e =
+        launch_fill_zero_f32(reinterpret_cast<float*>(tickets), 2 * p.rem, stream);
+    if (e != hipSuccess) return e;
+  } else if (p.meet == FwdMeet::kAtomics) {
+    const int64_t r0 = p.full * p.grid / ((N + 255) / 256) * 256;  // first row of a cut tile
+    const hipError_t e =
+        launch_fill_zero_f32(static_cast<float*>(Y) + r0 * N, (M - r0) * N, stream);
+    if (e != hipSuccess) return e;
   }
-  if (p.parts == 1) slots = nullptr;
   const FwdShape& c = kFwdShapes[p.shape];
   const int64_t tn = (N + c.bn - 1) / c.bn, ntiles = ((M + c.bm - 1) / c.bm) * tn;
   const dim3 grid((unsigned)p.grid);
@@ -794,14 +819,14 @@ hipError_t launch_tgemm_fwd_parts(const uint16_t* X, const uint8_t* codes, const
     else                                  \
       TM_FWD_L(GG, SS_, false, MA_, NW_); \
   } while (0)
-#define TM_FWD_S(GG, SS_)        \
-  do {                           \
-    if (p.shape == 0)            \
-      TM_FWD_B(GG, SS_, 4, 8);   \
-    else if (p.shape == 1)       \
-      TM_FWD_B(GG, SS_, 2, 4);   \
-    else                         \
-      TM_FWD_B(GG, SS_, 1, 4);   \
+#define TM_FWD_S(GG, SS_)            \
+  do {                               \
+    if (p.shape == 0)                \
+      TM_FWD_B(GG, SS_, 4, 8);       \
+    else if (p.shape == 2)           \
+      TM_FWD_B(GG, SS_, 1, 4);       \
+    else                             \
+      TM_FWD_B(GG, SS_, 2, 4);       \
   } while (0)
 #define TM_FWD(GG)      \
   case GG:              \

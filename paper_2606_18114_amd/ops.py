@@ -84,6 +84,7 @@ SIGNATURES = {
 # the calls of include/tmamba_parts.h
 SIGNATURES_PARTS = {
     "tm_tgemm_fwd_slots": (ctypes.c_int64, [_I64, _I64, _I64, _I32]),
+    "tm_tgemm_fwd_scratch": (ctypes.c_int64, [_I64, _I64, _I64, _I32, _I32]),
     "tm_tgemm_fwd_parts": (ctypes.c_int, [_P, _P, _P, _I64, _I64, _I64, _I32, _P, _I32, _P, _I64,
                                           _P, _I64, _P]),
     "tm_tgemm_bwd_dx_slots": (ctypes.c_int64, [_I64, _I64, _I64, _I32]),
@@ -309,9 +310,10 @@ def tgemm_fwd(X: torch.Tensor, codes: torch.Tensor, scales: torch.Tensor, g: int
               out_dtype: torch.dtype = torch.float32, *,
               workspace: Optional[torch.Tensor] = None) -> torch.Tensor:
     """Y[M, N] = X . (q * s)^T in float32, or rounded once to bfloat16
-    (out_dtype=torch.bfloat16), by ``tm_tgemm_fwd_parts``.  In float32 the two
-    parts of a tile cut in two meet in Y through a given workspace (uint8 of at
-    least ``fwd_workspace_bytes()`` bytes), as in ``tm_tgemm_fwd_ws``."""
+    (out_dtype=torch.bfloat16), by ``tm_tgemm_fwd_parts``: two calls give the
+    same bits (but where the memory for its scratch is not there).  workspace:
+    uint8 of at least ``fwd_workspace_bytes()`` bytes for the two parts of a
+    float32 tile that meet in Y; allocated by the call where not given."""
     _need(X, "X", _BF16, 2)
     _need(codes, "codes", _U8, 2)
     _need(scales, "scales", _F32, 2)
@@ -335,7 +337,7 @@ def tgemm_fwd(X: torch.Tensor, codes: torch.Tensor, scales: torch.Tensor, g: int
             raise ValueError(f"workspace has {workspace.numel()} bytes, {need} needed")
         if workspace.device != X.device:
             raise ValueError(f"workspace is on {workspace.device}, the operands on {X.device}")
-    slots = _slots(lib().tm_tgemm_fwd_slots(M, N, K, g), X.device)
+    slots = _slots(lib().tm_tgemm_fwd_scratch(M, N, K, g, int(out16)), X.device)
     st = lib().tm_tgemm_fwd_parts(_ptr(X), _ptr(codes), _ptr(scales), M, N, K, g, _ptr(Y),
                                   int(out16), _ptr(workspace),
                                   0 if workspace is None else workspace.numel(), _ptr(slots),

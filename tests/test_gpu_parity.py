@@ -352,6 +352,22 @@ def _fwd_no_workspace(X, c, s, g, Y):
     return Y
 
 
+def _fwd_workspace(X, c, s, g, Y):
+    """tm_tgemm_fwd_ws itself: two parts of a tile meet through tickets."""
+    ops = _ops()
+    M, K = X.shape
+    ws = torch.full((ops.fwd_workspace_bytes(),), 255, dtype=torch.uint8, device="cuda")
+    st = ops.lib().tm_tgemm_fwd_ws(X.data_ptr(), c.data_ptr(), s.data_ptr(), M, c.shape[0], K, g,
+                                   Y.data_ptr(), ws.data_ptr(), ws.numel(),
+                                   torch.cuda.current_stream().cuda_stream)
+    assert st == 0
+    # the tickets were used: both parts of every cut tile came, the first is done
+    tiles = -(-M // 256) * -(-c.shape[0] // 256)
+    words = ws.view(torch.int32)[:2 * (tiles % 256)].cpu()
+    assert bool((words[0::2] == 2).all()) and bool((words[1::2] == 1).all())
+    return Y
+
+
 def test_fwd_two_part_tiles_workspace_and_atomics():
     """Tiles cut in two along K meet through the workspace (the first part
     writes, the second adds): every element is written over a NaN-filled Y,
@@ -369,9 +385,11 @@ def test_fwd_two_part_tiles_workspace_and_atomics():
     outs = []
     for _ in range(2):
         Y = torch.full((M, N), float("nan"), device="cuda")
-        outs.append(host(ops.tgemm_fwd(X, c, s, g, Y=Y)))
+        outs.append(host(_fwd_workspace(X, c, s, g, Y)))
     assert np.isfinite(outs[0]).all()
     assert np.array_equal(outs[0].view(np.uint32), outs[1].view(np.uint32))
+    Y = torch.full((M, N), float("nan"), device="cuda")
+    assert O.rel_fro_error(host(ops.tgemm_fwd(X, c, s, g, Y=Y)), outs[0]) <= 1e-6
     Ya = host(_fwd_no_workspace(X, c, s, g, torch.full((M, N), float("nan"), device="cuda")))
     assert np.isfinite(Ya).all()
     diff = O.rel_fro_error(Ya, outs[0])
@@ -385,7 +403,9 @@ def test_fwd_two_part_tiles_workspace_and_atomics():
     Xd = dev_bf16(synth.f32_to_bf16_bits(Xi))
     cd, sd = torch.from_numpy(O.pack(qi)).cuda(), dev_f32(sc)
     ref = O.gemm_fwd(Xi, qi, sc, g)
-    Yw = host(ops.tgemm_fwd(Xd, cd, sd, g, Y=torch.full((M, N), float("nan"), device="cuda")))
+    Yw = host(_fwd_workspace(Xd, cd, sd, g, torch.full((M, N), float("nan"), device="cuda")))
+    Yo = host(ops.tgemm_fwd(Xd, cd, sd, g, Y=torch.full((M, N), float("nan"), device="cuda")))
+    np.testing.assert_array_equal(Yo, ref)
     Yn = host(_fwd_no_workspace(Xd, cd, sd, g, torch.full((M, N), float("nan"), device="cuda")))
     np.testing.assert_array_equal(Yw, ref)
     np.testing.assert_array_equal(Yn, ref)
