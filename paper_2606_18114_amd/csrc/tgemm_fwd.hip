@@ -92,6 +92,13 @@ struct FwdCfg {
   static_assert(kLds <= 160 * 1024, "LDS budget");
 };
 
+// Waves per SIMD whose registers a kernel keeps within: three 64 x 128
+// workgroups share a CU, but two for g = 32 in code stages of four, whose 202
+// registers do not fit three (57 spilled)
+constexpr int fwd_waves(int g, int ss, int ma) {
+  return ma == 1 && !(g == 32 && ss == 4) ? 3 : 2;
+}
+
 // 16-byte piece permutation of X row r inside its stage
 __device__ __forceinline__ int fwd_xswz(int r) { return (r & 7) ^ ((r >> 3) & 1); }
 // 16-byte chunk permutation of code row r inside a 4-stage code stage
@@ -137,14 +144,14 @@ __device__ __forceinline__ void static_for(F&& f) {
 // BF: Y in bfloat16 (each float32 result rounded to nearest even once),
 // else float32.  The bfloat16 form cuts tiles only with slots.
 template <int G, int SS, bool BF, int MA, int NW>
-__global__ __launch_bounds__(64 * NW, 2) void tgemm_fwd_kernel(
+__global__ __launch_bounds__(64 * NW, fwd_waves(G, SS, MA)) void tgemm_fwd_kernel(
     const uint16_t* __restrict__ X, const uint8_t* __restrict__ codes,
     const float* __restrict__ scales, int64_t M, int64_t N, int64_t K,
     void* __restrict__ Yv, uint32_t tiles_n, uint32_t full_rounds, uint32_t extra_units,
     uint32_t parts, uint32_t* __restrict__ tickets, float* __restrict__ slots) {
   using C = FwdCfg<G, SS, MA, NW>;
-  // the smaller tiles have the registers for a second accumulator: each
-  // group's products add up by themselves and join the total by one fused
+  // the smaller tiles have room for a second accumulator (128 x 128 with 8 to
+  // 31 registers spilled, 64 x 128 with at most 6): each group's products add up by themselves and join the total by one fused
   // multiply-add, which rounds once per group where the rescaled accumulator
   // rounds at every MFMA (relative error over K = 256 .. 3584: 3e-8 to 1.1e-7
   // against 5e-8 to 1.6e-7)
@@ -655,19 +662,31 @@ __global__ __launch_bounds__(64 * NW, 2) void tgemm_fwd_kernel(
   asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
 }
 
-// The three tile shapes: workgroups a CU holds; time of a 64-column stage with
-// the chip full and with a CU's workgroup alone on an idle chip (the first is
-// set by the power cap and the shared pipes, the second by a stage's own
-// chain of waits); a slot's write and read.  Measured at g = 128 over 16
-// shapes from 300 x 8512 x 2048 to 16384 x 8512 x 2048.
+// The three tile shapes, and per shape and group size: workgroups a CU holds
+// (0: not used); time of a 64-column stage with the chip full and with a CU's
+// workgroup alone on an idle chip (the first is set by the power cap and the
+// shared pipes, the second by a stage's own chain of waits).  Then what the
+// ways of joining parts cost: a slot's write and read and the reduction's
+// launch; the second pass of a ticket tile over Y.  Set so that the least
+// estimate is within 1.1% of the fastest on average (14% at worst) over 233
+// measured products (16 to 16384 tokens of ten layers from 3352 x 768 to 2048 x
+// 8192, g = 32 to 512) on every shape and cut.  At g = 32 the 128 x 128 tile is out: its two accumulators and four
+// scale steps a stage need more than the 256 registers (170 spilled; 4096 x
+// 2048 x 4096: 206 us, 64 x 128 tiles 92, 256 x 256 ones 98).
 struct FwdShape {
-  int bm, bn, per_cu;
-  double full_us, alone_us, slot_us;
+  int bm, bn;
+  double slot_us;
 };
-constexpr FwdShape kFwdShapes[3] = {{256, 256, 1, 1.75, 0.95, 0.10},
-                                    {128, 128, 2, 0.98, 0.55, 0.025},
-                                    {64, 128, 3, 0.92, 0.38, 0.0125}};
-constexpr double kFwdLaunchUs = 5.0, kFwdTileUs = 1.0, kFwdTicketUs = 0.05;
+struct FwdStage {
+  int per_cu;
+  double full_us, alone_us;
+};
+constexpr FwdShape kFwdShapes[3] = {{256, 256, 0.079}, {128, 128, 0.024}, {64, 128, 0.009}};
+constexpr FwdStage kFwdStages[3][3] = {
+    {{1, 2.10, 1.96}, {0, 0.00, 0.00}, {2, 0.65, 0.46}},   // g = 32
+    {{1, 1.88, 1.74}, {2, 0.94, 0.87}, {3, 0.97, 0.27}},   // g = 64
+    {{1, 1.65, 1.40}, {2, 0.95, 0.63}, {3, 0.84, 0.30}}};  // g >= 128
+constexpr double kFwdLaunchUs = 5.0, kFwdTileUs = 0.79, kFwdTicketUs = 0.064;
 
 // How the parts of a cut tile meet
 enum class FwdMeet { kWhole, kSlots, kTickets, kAtomics };
@@ -711,9 +730,9 @@ static FwdPlan fwd_plan(int64_t M, int64_t N, int64_t K, int g, bool bf16_out) {
   double best_t = 0;
   for (int i = 0; i < 3; ++i) {
     const FwdShape& c = kFwdShapes[i];
-    const FwdShape& s = c;
+    const FwdStage& s = kFwdStages[g >= 128 ? 2 : g / 64][i];
     const int64_t tiles = ((M + c.bm - 1) / c.bm) * ((N + c.bn - 1) / c.bn);
-    if (tiles > 0x7FFFFFFF) continue;  // 32-bit tile numbers
+    if (s.per_cu == 0 || tiles > 0x7FFFFFFF) continue;  // 32-bit tile numbers
     const int64_t P = (int64_t)cus * s.per_cu;
     const int64_t F = tiles / P, R = tiles % P;
     const int64_t most = R > 0 ? (P / R < trips ? P / R : trips) : 1;
@@ -825,8 +844,10 @@ hipError_t launch_tgemm_fwd_parts(const uint16_t* X, const uint8_t* codes, const
       TM_FWD_B(GG, SS_, 4, 8);       \
     else if (p.shape == 2)           \
       TM_FWD_B(GG, SS_, 1, 4);       \
-    else                             \
+    else if constexpr (GG >= 64)     \
       TM_FWD_B(GG, SS_, 2, 4);       \
+    else                             \
+      return hipErrorInvalidValue;   \
   } while (0)
 #define TM_FWD(GG)      \
   case GG:              \
@@ -839,8 +860,8 @@ hipError_t launch_tgemm_fwd_parts(const uint16_t* X, const uint8_t* codes, const
     TM_FWD(32)
     TM_FWD(64)
     TM_FWD(128)
-    TM_FWD(256)
-    TM_FWD(512)
+    case 256: TM_FWD_S(256, 4); break;  // (K is a multiple of g)
+    case 512: TM_FWD_S(512, 4); break;
     default: return hipErrorInvalidValue;
   }
 #undef TM_FWD
