@@ -182,8 +182,12 @@ __global__ __launch_bounds__(256) void dx_prep_kernel(
 }
 
 // BF: dX in bfloat16 (each float32 sum rounded to nearest even once), else
-// float32; the bfloat16 form always has slots for its parts
-template <int G, bool BF>
+// float32; ADD (float32): parts without slots add up in dX.  One way of
+// writing cut tiles per instantiation: with slots and atomics in one the float32
+// form spilled 436 bytes a lane at g = 128 (44 and 188 now).  16384 tokens, 8512
+// -> 2048: 632 -> 602 us without slots, 700 -> 680 through the binding (power
+// capped); 2048 tokens: 113 -> 108 with slots, 221 -> 196 without.
+template <int G, bool BF, bool ADD>
 __global__ __launch_bounds__(256) void tgemm_bwd_dx_f16_kernel(
     const uint16_t* __restrict__ dY16, const int32_t* __restrict__ rexp,
     const uint32_t* __restrict__ sparts, int nparts, const uint32_t* __restrict__ codes,
@@ -519,7 +523,10 @@ __global__ __launch_bounds__(256) void tgemm_bwd_dx_f16_kernel(
       for (int i = 0; i < 16; ++i)
         ex[i] = -(rxv[wm * 128 + 32 * a + 4 * h + 8 * (i / 4) + (i % 4)] + tsc);
     };
-    auto val = [&](int a, int b, int i) { return ldexpf(acc[a][b][i], ex[i]); };
+    auto val = [&](int a, int b, int i) {
+      // (the opaque copy where it halves the spills: 360 to 200 bytes at g = 256)
+      return ldexpf(ADD && (G < 64 || G > 128) ? acc_value(acc[a][b][i]) : acc[a][b][i], ex[i]);
+    };
     using Out = std::conditional_t<BF, uint16_t, float>;
     const int rows_left = rows - wm * 128;
     const int64_t col0 = k0 + wk * 128;
@@ -532,9 +539,9 @@ __global__ __launch_bounds__(256) void tgemm_bwd_dx_f16_kernel(
         else
           *p = v;
       });
-    else if (BF || slots)
+    else if constexpr (!ADD)
       slot_store(slots + (int64_t)bid * kSlotFloats, rows_left, cols_left, prep, val);
-    else if constexpr (!BF)
+    else
       tile_store(out, K, rows_left, cols_left, prep, val,
                  [](float* p, float v) { atomicAdd(p, v); });
   }
@@ -594,16 +601,19 @@ hipError_t launch_tgemm_bwd_dx_f16_parts(const void* dY, bool f32_in, uint16_t* 
   }
   const auto* cw = reinterpret_cast<const uint32_t*>(codes);
   const dim3 grid((unsigned)t.grid), block(256);
-#define TM_DX_CASE(GG, BF_)                                                                     \
-  hipLaunchKernelGGL((tgemm_bwd_dx_f16_kernel<GG, BF_>), grid, block, 0, stream, dY16, rexp, sparts, kScaleParts, cw,   \
+  const bool add = t.parts > 1 && !slots;
+#define TM_DX_CASE(GG, BF_, ADD_)                                                               \
+  hipLaunchKernelGGL((tgemm_bwd_dx_f16_kernel<GG, BF_, ADD_>), grid, block, 0, stream, dY16, rexp, sparts, kScaleParts, cw,   \
                      scales, M, N, K, dX, (uint32_t)tk, (uint32_t)t.full, (uint32_t)t.rem,      \
                      (uint32_t)t.parts, t.per, slots)
-#define TM_DX_G(GG)            \
-  case GG:                     \
-    if (bf16_out)              \
-      TM_DX_CASE(GG, true);    \
-    else                       \
-      TM_DX_CASE(GG, false);   \
+#define TM_DX_G(GG)                 \
+  case GG:                          \
+    if (bf16_out)                   \
+      TM_DX_CASE(GG, true, false);  \
+    else if (add)                   \
+      TM_DX_CASE(GG, false, true);  \
+    else                            \
+      TM_DX_CASE(GG, false, false); \
     break;
   switch (g) {
     TM_DX_G(32)
