@@ -73,6 +73,87 @@ def test_weight_grad(M, N, K, g):
     assert _rel(acc, ref + 1) <= tol + 2.0 ** -24
 
 
+# More than 256 tiles of dX (dW) and a remainder: without scratch the leftover
+# tiles are cleared and their parts add up by atomics; ragged and whole edges,
+# parts of few stages
+@pytest.mark.parametrize("M,N,K,g", [(4300, 520, 4160, 64), (4352, 1032, 4096, 256),
+                                     (4170, 200, 4224, 128)])
+@pytest.mark.parametrize("precision", ["f16", "exact"])
+def test_input_grad_without_scratch(M, N, K, g, precision):
+    print(f"[parts] dX no scratch {precision} M={M} N={N} K={K} g={g}", flush=True)
+    _, dy, codes, s, what = _operands(M, N, K, g)
+    dyb = dy.to(torch.bfloat16)
+    dX = torch.full((M, K), float("nan"), device="cuda")
+    head = (dyb.data_ptr(), codes.data_ptr(), s.data_ptr(), M, N, K, g, dX.data_ptr())
+    stream = torch.cuda.current_stream().cuda_stream
+    if precision == "f16":
+        ws = torch.empty(ops.dx_f16_workspace_bytes(M, N), dtype=torch.uint8, device="cuda")
+        st = ops.lib().tm_tgemm_bwd_dx_f16(*head, ws.data_ptr(), ws.numel(), stream)
+    else:
+        st = ops.lib().tm_tgemm_bwd_dx(*head, stream)
+    assert st == 0
+    assert _rel(dX, dyb.double() @ what) <= (2.0 ** -11 if precision == "f16" else 2.0 ** -15)
+    # the same products in another order
+    with_scratch = ops.tgemm_bwd_dx(dyb, codes, s, g, precision=precision)
+    assert _rel(dX, with_scratch.double()) <= 2.0 ** -23 * N ** 0.5
+
+
+@pytest.mark.parametrize("M,N,K", [(300, 4104, 4160), (1000, 4352, 4096), (65, 4360, 4224)])
+@pytest.mark.parametrize("accumulate", [0, 1])
+def test_weight_grad_without_scratch(M, N, K, accumulate):
+    print(f"[parts] dW no scratch M={M} N={N} K={K} accumulate={accumulate}", flush=True)
+    x, dy, _, _, _ = _operands(M, N, K, 64)
+    dyb = dy.to(torch.bfloat16)
+    dW = torch.full((N, K), 1.0 if accumulate else float("nan"), device="cuda")
+    st = ops.lib().tm_tgemm_bwd_dw_ste(dyb.data_ptr(), x.data_ptr(), M, N, K, dW.data_ptr(),
+                                       accumulate, torch.cuda.current_stream().cuda_stream)
+    assert st == 0
+    ref = dyb.double().t() @ x.double() + accumulate
+    # float32 sums of exact products; a sum that starts at 1 rounds to its step
+    # at each of at most 256 parts
+    tol = 2.0 ** -23 * max(M, 16) ** 0.5
+    assert _rel(dW, ref) <= tol + accumulate * 2.0 ** -20
+
+
+@pytest.mark.parametrize("M,N,K,g", [(2050, 2056, 512, 512), (300, 8512, 2048, 128)])
+def test_no_memory_for_scratch(M, N, K, g, monkeypatch):
+    """Where the scratch cannot be allocated the calls do without it."""
+    print(f"[parts] no memory for scratch M={M} N={N} K={K} g={g}", flush=True)
+    x, dy, codes, s, what = _operands(M, N, K, g)
+    dyb = dy.to(torch.bfloat16)
+    L, none = ops.lib(), []
+    sizes = {L.tm_tgemm_fwd_scratch(M, N, K, g, 0), L.tm_tgemm_fwd_scratch(M, N, K, g, 1),
+             L.tm_tgemm_bwd_dx_slots(M, N, K, 0), L.tm_tgemm_bwd_dx_slots(M, N, K, 1),
+             L.tm_tgemm_bwd_dw_slots(M, N, K)} - {0, ops.dx_f16_workspace_bytes(M, N)}
+
+    def calls():
+        return [ops.tgemm_fwd(x, codes, s, g), ops.tgemm_fwd(x, codes, s, g,
+                                                             out_dtype=torch.bfloat16),
+                ops.tgemm_bwd_dx(dyb, codes, s, g), ops.tgemm_bwd_dx(dyb, codes, s, g,
+                                                                     precision="exact"),
+                ops.layer_input_grad(dy, codes, s, g)[0], ops.layer_input_grad(dyb, codes, s, g)[0],
+                ops.layer_input_grad(dyb, codes, s, g, precision="exact")[0],
+                ops.tgemm_bwd_dw_ste(dyb, x)]
+    want = calls()
+    real = torch.empty
+
+    def empty(*a, **kw):
+        if kw.get("dtype") == torch.uint8 and a[0] in sizes:
+            none.append(a[0])
+            raise torch.OutOfMemoryError("none left")
+        return real(*a, **kw)
+    monkeypatch.setattr(torch, "empty", empty)
+    got = calls()
+    monkeypatch.undo()
+    assert len(none) >= 5
+    for a, b in zip(got, want):
+        assert a.dtype == b.dtype
+        # another order of the float32 sums; in bfloat16 a rounding may fall
+        # the other way
+        assert _rel(a, b.double()) <= (2.0 ** -9 if a.dtype == torch.bfloat16
+                                       else 2.0 ** -23 * max(M, N, K) ** 0.5)
+
+
 # (tokens, out features, in features, g): the forward's three tile shapes, cut
 # and whole, with code stages of one and four operand stages
 FORWARD = [(1, 64, 64, 32), (16, 256, 512, 128), (70, 1000, 320, 64), (300, 8512, 2048, 128),
