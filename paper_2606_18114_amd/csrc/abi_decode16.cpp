@@ -64,9 +64,10 @@ tm_status tm_mixer_gate_part(const float* zxbcdt, int32_t B, int32_t nheads, int
   if (!aligned(partial, 4)) return TM_EALIGN;
   const int64_t h = nheads, di = 64 * h, cd = di + 256;
   const Span p = span(partial, B * h * 4);
-  const Span others[6] = {span(zxbcdt, B * (2 * di + 256 + h) * 4), span(conv_state, B * cd * 8),
-                          span(conv_pos, 4), span(ssm_state, B * di * 256), span(gated, B * di * 4),
-                          span(conv_w, cd * 16)};
+  const Span others[10] = {span(zxbcdt, B * (2 * di + 256 + h) * 4), span(conv_state, B * cd * 8),
+                           span(conv_pos, 4), span(ssm_state, B * di * 256),
+                           span(gated, B * di * 4), span(conv_w, cd * 16), span(conv_b, cd * 4),
+                           span(dt_bias, h * 4), span(A_log, h * 4), span(D, h * 4)};
   for (const Span& o : others)
     if (overlap(p, o)) return TM_EINVAL;
   return hip_status(tmk::launch_mixer_gate_part(zxbcdt, B, nheads, conv_state, conv_pos,

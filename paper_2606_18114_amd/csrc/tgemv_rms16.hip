@@ -328,7 +328,7 @@ __global__ __launch_bounds__(64 * kR16Waves) void tgemv_rms16_kernel(
   }
 }
 
-// dst[b] = src[b] (dst may be NULL or src) and part[b] = the row's sum of squares
+// dst[b] = src[b] (dst may be NULL) and part[b] = the row's sum of squares
 __global__ __launch_bounds__(256) void rows_sumsq_kernel(const float* src, int64_t D, float* dst,
                                                          float* __restrict__ part) {
   __shared__ float wsum[4];

@@ -1,5 +1,5 @@
-// Host-only stand-ins for the kernel launchers, linked with abi.cpp into a
-// sanitizer build of the C ABI's argument checks.  The checks run before any
+// Host-only stand-ins for the kernel launchers, linked with the C ABI's
+// translation units (abi*.cpp) into a sanitizer build of the C ABI's argument checks.  The checks run before any
 // launch, and the tests that use this build pass only arguments the checks
 // reject, so reaching a stub is itself a failure: each one aborts.
 #include <cstdio>
@@ -98,6 +98,43 @@ hipError_t launch_decode_stack(const DecodeStackDesc&, const float*, uint16_t*, 
 hipError_t launch_residual_rmsnorm(float*, const float*, int, int64_t, const float*, float,
                                    uint16_t*, hipStream_t) {
   reached("residual_rmsnorm");
+}
+
+// scratch sizes: any tile counts as cut from 2048 tokens on
+static int64_t cut_bytes(int64_t M) { return M >= 2048 ? int64_t(1) << 20 : 0; }
+int64_t fwd_scratch_bytes(int64_t M, int64_t, int64_t, int, bool) { return cut_bytes(M); }
+int64_t bwd_dx_slot_bytes(int64_t M, int64_t, int64_t) { return cut_bytes(M); }
+int64_t bwd_dx_f16_slot_bytes(int64_t M, int64_t, int64_t) { return cut_bytes(M); }
+int64_t bwd_dw_slot_bytes(int64_t M, int64_t, int64_t) { return cut_bytes(M); }
+hipError_t launch_tgemm_fwd_parts(const uint16_t*, const uint8_t*, const float*, int64_t, int64_t,
+                                  int64_t, int, void*, bool, uint32_t*, void*, bool, hipStream_t) {
+  reached("tgemm_fwd_parts");
+}
+hipError_t launch_tgemm_bwd_dx_parts(const uint16_t*, const uint8_t*, const float*, int64_t,
+                                     int64_t, int64_t, int, void*, bool, float*, hipStream_t) {
+  reached("tgemm_bwd_dx_parts");
+}
+hipError_t launch_tgemm_bwd_dx_f16_parts(const void*, bool, uint16_t*, const uint8_t*,
+                                         const float*, int64_t, int64_t, int64_t, int, void*,
+                                         bool, void*, float*, hipStream_t) {
+  reached("tgemm_bwd_dx_f16_parts");
+}
+hipError_t launch_tgemm_bwd_dw_parts(const uint16_t*, const uint16_t*, int64_t, int64_t, int64_t,
+                                     float*, int, float*, hipStream_t) {
+  reached("tgemm_bwd_dw_parts");
+}
+hipError_t launch_rows_sumsq(const float*, int, int64_t, float*, float*, hipStream_t) {
+  reached("rows_sumsq");
+}
+hipError_t launch_tgemv_rms16(const float*, const float*, int, const float*, float, const uint8_t*,
+                              const uint16_t*, int, int64_t, int64_t, int, float*, int, float*,
+                              int*, hipStream_t) {
+  reached("tgemv_rms16");
+}
+hipError_t launch_mixer_gate_part(const float*, int, int, uint16_t*, const int*, uint16_t*,
+                                  const float*, const float*, const float*, const float*,
+                                  const float*, float*, float*, hipStream_t) {
+  reached("mixer_gate_part");
 }
 
 }  // namespace tmk

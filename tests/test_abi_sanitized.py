@@ -1,9 +1,10 @@
 """The C ABI's host-side argument checks under AddressSanitizer and
 UndefinedBehaviorSanitizer.
 
-``abi.cpp`` is compiled with g++ for the host only (the kernel launchers are
-replaced by stubs that abort if reached) into a sanitized shared library, and
-``tests/test_abi_host.py`` runs against it in a child Python with the ASan
+``abi.cpp``, ``abi_parts.cpp`` and ``abi_decode16.cpp`` are compiled with g++
+for the host only (the kernel launchers are replaced by stubs that abort if
+reached) into a sanitized shared library, and ``tests/test_abi_host.py`` and
+``tests/test_abi_host_parts.py`` run against it in a child Python with the ASan
 runtime preloaded.  Any out-of-bounds access, overflow or undefined
 behaviour in the checks fails the child run.
 """
@@ -34,7 +35,8 @@ def sanitized_lib(tmp_path_factory):
            "-fsanitize=address,undefined", "-fno-sanitize-recover=undefined",
            "-Wall", "-Wextra", "-Werror", "-D__HIP_PLATFORM_AMD__",
            "-I", os.path.join(ROCM, "include"), "-I", os.path.join(ROOT, "include"),
-           os.path.join(ROOT, "paper_2606_18114_amd", "csrc", "abi.cpp"),
+           *(os.path.join(ROOT, "paper_2606_18114_amd", "csrc", f)
+             for f in ("abi.cpp", "abi_parts.cpp", "abi_decode16.cpp")),
            os.path.join(ROOT, "tests", "abi_launch_stubs.cpp"),
            "-L", os.path.join(ROCM, "lib"), "-lamdhip64", "-o", out]
     proc = subprocess.run(cmd, capture_output=True, text=True)
@@ -49,7 +51,8 @@ def test_abi_checks_under_sanitizers(sanitized_lib):
     env["UBSAN_OPTIONS"] = "print_stacktrace=1:halt_on_error=1"
     env["TM_ABI_TEST_LIB"] = sanitized_lib
     proc = subprocess.run([sys.executable, "-m", "pytest", "-q", "-p", "no:cacheprovider",
-                           os.path.join(ROOT, "tests", "test_abi_host.py")],
+                           *(os.path.join(ROOT, "tests", f)
+                             for f in ("test_abi_host.py", "test_abi_host_parts.py"))],
                           capture_output=True, text=True, env=env, cwd=ROOT, timeout=600)
     assert proc.returncode == 0, proc.stdout[-3000:] + proc.stderr[-3000:]
     assert "passed" in proc.stdout
