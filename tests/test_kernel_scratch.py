@@ -58,6 +58,7 @@ def scratch(tmp_path_factory):
     *((f"tgemm_bwd_dx_f16_kernel<{g}, {out}, false>", 112)
       for g in (32, 64, 128, 256, 512) for out in ("true", "false")),
     *((f"tgemm_bwd_dx_f16_kernel<{g}, false, true>", 244) for g in (32, 64, 128, 256, 512)),
+    ("tgemm_bwd_dw_kernel", 160),
 ])
 def test_scratch(scratch, kernel, most):
     assert scratch["tmk::" + kernel] <= most
