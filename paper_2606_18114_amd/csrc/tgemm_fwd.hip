@@ -150,11 +150,11 @@ __global__ __launch_bounds__(64 * NW, fwd_waves(G, SS, MA)) void tgemm_fwd_kerne
     void* __restrict__ Yv, uint32_t tiles_n, uint32_t full_rounds, uint32_t extra_units,
     uint32_t parts, uint32_t* __restrict__ tickets, float* __restrict__ slots) {
   using C = FwdCfg<G, SS, MA, NW>;
-  // the smaller tiles have room for a second accumulator (128 x 128 with 8 to
-  // 31 registers spilled, 64 x 128 with at most 6): each group's products add up by themselves and join the total by one fused
-  // multiply-add, which rounds once per group where the rescaled accumulator
-  // rounds at every MFMA (relative error over K = 256 .. 3584: 3e-8 to 1.1e-7
-  // against 5e-8 to 1.6e-7)
+  // the smaller tiles have room for a second accumulator (128 x 128 with at most
+  // 15 registers spilled): each group's products add up by themselves and join
+  // the total by one fused multiply-add, which rounds once per group where the
+  // rescaled accumulator rounds at every MFMA (relative error over K = 256 ..
+  // 3584: 3e-8 to 1.1e-7 against 5e-8 to 1.6e-7)
   constexpr bool kTwo = MA <= 2;
   constexpr int kFwdXStage = C::kXStage, kFwdBM = C::kBM, kFwdBN = C::kBN;
   __shared__ __attribute__((aligned(1024))) uint8_t lds[C::kLds];
@@ -556,17 +556,25 @@ __global__ __launch_bounds__(64 * NW, fwd_waves(G, SS, MA)) void tgemm_fwd_kerne
       }
       uint8_t* ytile = reinterpret_cast<uint8_t*>(Yv) + (mrow * N + n0) * ES;
       const bool full_m = mrow + 32 * MA <= M;
+      // The small tiles take opaque copies: the compiler would hold the lane
+      // offsets of every form over the whole unit, spill them and read them
+      // back in front of the stores (700 x 8512 x 2048: 31.7 -> 31.2 us, 4096 x
+      // 2048 x 4096: 64.4 -> 62.5).  The 256 x 256 tile has the registers, and is
+      // slower so (16384 x 8512 x 2048: 497 -> 508).
+      int el = l32;
+      uint32_t eh = h;
+      if constexpr (kTwo) asm volatile("" : "+v"(el), "+v"(eh));
 #pragma unroll
       for (int b = 0; b < 2; ++b) {
-        const int nl = wn * 64 + b * 32 + l32;  // column in the tile
+        const int nl = wn * 64 + b * 32 + el;  // column in the tile
         if (n0 + nl >= N) continue;
         const float f = kTwo ? 1.f : 0.5f * cref[b];
-        uint8_t* ylane = ytile + ((int64_t)(4 * h) * N + nl) * ES;
+        uint8_t* ylane = ytile + ((int64_t)(4 * eh) * N + nl) * ES;
         if (!BF && part) {
           int64_t pv = N * 4;
           asm volatile("" : "+v"(pv));
           uint8_t* yp = ylane;
-          int64_t row = mrow + 4 * h;
+          int64_t row = mrow + 4 * eh;
 #pragma unroll
           for (int a = 0; a < MA; ++a)
 #pragma unroll
@@ -595,7 +603,7 @@ __global__ __launch_bounds__(64 * NW, fwd_waves(G, SS, MA)) void tgemm_fwd_kerne
             uint32_t pv = (uint32_t)N * ES;
             asm volatile("" : "+v"(pv));
             const uint32_t pv4 = 4u * pv;
-            uint32_t o = (uint32_t)((4 * h) * N + nl) * ES;
+            uint32_t o = (uint32_t)((4 * eh) * N + nl) * ES;
 #pragma unroll
             for (int a = 0; a < MA; ++a)
 #pragma unroll
@@ -626,7 +634,7 @@ __global__ __launch_bounds__(64 * NW, fwd_waves(G, SS, MA)) void tgemm_fwd_kerne
           int64_t pv = N * ES;
           asm volatile("" : "+v"(pv));
           uint8_t* yp = ylane;
-          int64_t row = mrow + 4 * h;
+          int64_t row = mrow + 4 * eh;
 #pragma unroll
           for (int a = 0; a < MA; ++a)
 #pragma unroll

@@ -59,6 +59,12 @@ def scratch(tmp_path_factory):
       for g in (32, 64, 128, 256, 512) for out in ("true", "false")),
     *((f"tgemm_bwd_dx_f16_kernel<{g}, false, true>", 244) for g in (32, 64, 128, 256, 512)),
     ("tgemm_bwd_dw_kernel", 160),
+    # <g, code stage, bfloat16 out, shape>: the forward's 256 x 256 and 64 x 128
+    # tiles hold everything in registers
+    *((f"tgemm_fwd_kernel<{g}, {ss}, {out}, {shape}>", most)
+      for g, ss in ((32, 4), (32, 1), (64, 4), (64, 1), (128, 4), (128, 1), (256, 4), (512, 4))
+      for out in ("true", "false")
+      for shape, most in (("4, 8", 0), ("1, 4", 0), ("2, 4", 32)) if g > 32 or shape != "2, 4"),
 ])
 def test_scratch(scratch, kernel, most):
     assert scratch["tmk::" + kernel] <= most
