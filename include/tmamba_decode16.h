@@ -1,8 +1,8 @@
 /*
  * tmamba_decode16.h — the three calls of a decode layer for batches of 5 to
- * 16 rows, whose normalizations need no launch of their own: each call leaves
- * the partial sums of squares that the next one normalizes with.  Shapes,
- * layouts and status codes as in tmamba.h.
+ * 16 rows, whose normalizations need no launch of their own: a call takes the
+ * partial sums of squares that the one before left, or sums the squares
+ * itself.  Shapes, layouts and status codes as in tmamba.h.
  */
 #ifndef TMAMBA_DECODE16_H
 #define TMAMBA_DECODE16_H
@@ -23,11 +23,11 @@ tm_status tm_rows_sumsq(const float* src, int32_t B, int64_t D, float* dst, floa
 /*
  * x = bf16(src / sqrt(sum(part) / K + eps) * norm_w) per batch row (B <= 16,
  * part [B, nparts]; NULL with nparts = 0: the squares of src are summed by this
- * call), y [B, N] = x . What^T, or += it with accumulate = 1;
- * g = 64, 128 or 256, K <= 4096.  With B >= 9 the sums are taken in the order
- * of tm_tgemv, and the squares, with part NULL, in that of
- * tm_residual_rmsnorm: the same bits as those two calls.  part_out (NULL or [B, ceil(N / 16)]): partial sums of
- * the squares of y as written.  advance (NULL or a mixer's conv_pos): the
+ * call), y [B, N] = x . What^T, or += it with accumulate = 1; g = 64, 128 or
+ * 256, K <= 4096.  With B >= 9 the sums are taken in the order of tm_tgemv,
+ * and the squares, with part NULL, in that of tm_residual_rmsnorm: the same
+ * bits as those two calls.  part_out (NULL or [B, ceil(N / 16)]): partial sums
+ * of the squares of y as written.  advance (NULL or a mixer's conv_pos): the
  * ring position moves on by one slot.
  */
 tm_status tm_tgemv_rms16(const float* src, const float* part, int32_t nparts,

@@ -162,9 +162,10 @@ hipError_t launch_mixer_gate_part(const float* zxbcdt, int B, int nheads, uint16
                                   const float* D, float* gated, float* partial,
                                   hipStream_t stream);
 // launch_tgemv_rms for up to 16 rows at g = 64, 128, 256, the rows' sums of
-// squares given as nparts partial sums each (part [B, nparts]).  part_out (may
-// be NULL): [B, ceil(N / 16)] partial sums of the squares of y as written.
-// advance (may be NULL): a ring position, moved on by one slot.
+// squares given as nparts partial sums each (part [B, nparts]), or summed here
+// (part NULL).  part_out (may be NULL): [B, ceil(N / 16)] partial sums of the
+// squares of y as written.  advance (may be NULL): a ring position, moved on by
+// one slot.
 constexpr int64_t kRms16MaxK = 4096;  // x of 16 rows in LDS
 hipError_t launch_tgemv_rms16(const float* src, const float* part, int nparts, const float* nw,
                               float eps, const uint8_t* codes, const uint16_t* s16, int B,
