@@ -74,9 +74,9 @@ class Step:
                 for k in ("codes", "s", "s16", "zc", "Y", "dX", "dX2", "dW", "y")}
 
 
-# bit-exact: codes, scales, counts, the GEMV, and Y (its tiles are cut into
-# two parts at most here, and two float32 partial sums add exactly in either
-# order onto the cleared rows); dX and dW add many parts with atomics
+# bit-exact: codes, scales, counts, the GEMV, and Y; dX and dW, whose tiles are
+# cut into many parts, to float32 rounding (the parts add up by atomics where
+# there is no memory for their scratch)
 EXACT = ("codes", "s", "s16", "zc", "Y", "y")
 
 
@@ -85,7 +85,7 @@ def _compare(got, ref, label):
         a, b = got[k], ref[k]
         if k in EXACT:
             assert torch.equal(a, b), f"{label}: {k} differs"
-        else:  # dX (both forms), dW: float32 atomics over the cut contraction
+        else:  # dX (both forms), dW
             rel = float((a.double() - b.double()).norm() / b.double().norm())
             assert rel <= 1e-6, f"{label}: {k} rel {rel:.2e}"
 

@@ -198,3 +198,48 @@ def test_float32_gradient_rounding():
     nan = ref.isnan()
     assert torch.equal(got.isnan(), nan)
     assert torch.equal(got[~nan].view(torch.int16), ref[~nan].view(torch.int16))
+
+
+# the forward's parts meet through tickets, and in slots; dX's and dW's in slots
+@pytest.mark.parametrize("M,N,K,g", [(4352, 4096, 512, 128), (2048, 8512, 2048, 128)])
+def test_scratch_in_graphs_and_on_two_streams(M, N, K, g):
+    """The calls' scratch under capture (replayed with eager work between) and
+    in use on two streams at once: the bits of the eager run."""
+    print(f"[parts] scratch in graphs and streams M={M} N={N} K={K} g={g}", flush=True)
+    x, dy, codes, s, _ = _operands(M, N, K, g)
+    dyb = dy.to(torch.bfloat16)
+
+    def outputs():
+        return [torch.full((M, N), float("nan"), device="cuda"),
+                torch.full((M, K), float("nan"), device="cuda"),
+                torch.full((N, K), float("nan"), device="cuda")]
+
+    def run(Y, dX, dW):
+        ops.tgemm_fwd(x, codes, s, g, Y=Y)
+        ops.tgemm_bwd_dx(dyb, codes, s, g, dX=dX)
+        ops.tgemm_bwd_dw_ste(dyb, x, dW)
+        return Y, dX, dW
+    want = run(*outputs())
+    torch.cuda.synchronize()
+    sides = [torch.cuda.Stream(), torch.cuda.Stream()]
+    outs = [outputs(), outputs()]
+    torch.cuda.synchronize()
+    for _ in range(3):
+        for side, out in zip(sides, outs):
+            with torch.cuda.stream(side):
+                run(*out)
+    torch.cuda.synchronize()
+    for out in outs:
+        assert all(torch.equal(a, b) for a, b in zip(out, want))
+    graph = torch.cuda.CUDAGraph()
+    out = outs[0]
+    with torch.cuda.graph(graph):
+        run(*out)
+    for rep in range(3):
+        for t in out:
+            t.fill_(float("nan"))
+        run(*outs[1])  # eager work in scratch of its own
+        torch.cuda.synchronize()
+        graph.replay()
+        torch.cuda.synchronize()
+        assert all(torch.equal(a, b) for a, b in zip(out, want)), f"replay {rep}"
