@@ -95,14 +95,16 @@ __device__ __forceinline__ uint32_t dw_off(int r, int c) {
   return (uint32_t)(r * 512 + 32 * ((c >> 4) ^ dw_swz(r)) + 2 * (c & 15));
 }
 
-// One instantiation for every way of writing (stores, slots, sums in place): it
-// spills 152 bytes a lane outside the stages, a form that only stores 192 and is
-// the slower one (2048 tokens x 8512 x 2048: 95 us against 92; 1000 x 3352 x
-// 768: 40.4 against 38.6; 16 x 256 x 512: 17.5 against 16.2; 16384 tokens equal).
+// ACC: whole tiles are added to dW (accumulate), else stored; either form has
+// the slots and the atomics of cut tiles.  Spills, outside the stages: 92 bytes a
+// lane, 84 with ACC; with both ways of writing whole tiles in one kernel 152, a
+// form without the atomics 192.  2048 tokens x 8512 x 2048: 88.5 us (91.9 in one
+// kernel); 1000 x 3352 x 768: 36.2 (38.6).
+template <bool ACC>
 __global__ __launch_bounds__(256) void tgemm_bwd_dw_kernel(
     const uint16_t* __restrict__ dY, const uint16_t* __restrict__ X, int64_t M, int64_t N,
-    int64_t K, float* __restrict__ dW, int accumulate, uint32_t tiles_k, uint32_t full,
-    uint32_t rem, uint32_t parts, int per, float* __restrict__ slots) {
+    int64_t K, float* __restrict__ dW, uint32_t tiles_k, uint32_t full, uint32_t rem,
+    uint32_t parts, int per, float* __restrict__ slots) {
   __shared__ __attribute__((aligned(1024))) uint8_t lds[kDwLds];
 
   const int lane = threadIdx.x & 63;
@@ -332,15 +334,15 @@ __global__ __launch_bounds__(256) void tgemm_bwd_dw_kernel(
     const int rows_left = (int)(N - row0 < 256 ? N - row0 : 256);
     const int cols_left = (int)(K - col0 < 256 ? K - col0 : 256);
     float* out = dW + row0 * K + col0;
-    if (whole && !accumulate)
-      tile_store(out, K, rows_left, cols_left, none, val, [](float* p, float v) { *p = v; });
-    else if (!whole && slots)
+    if (!whole && slots)
       slot_store(slots + (int64_t)bid * kSlotFloats, rows_left, cols_left, none, val);
-    else if (whole)
-      tile_store(out, K, rows_left, cols_left, none, val, [](float* p, float v) { *p += v; });
-    else
+    else if (!whole)
       tile_store(out, K, rows_left, cols_left, none, val,
                  [](float* p, float v) { atomicAdd(p, v); });
+    else if constexpr (ACC)
+      tile_add(out, K, rows_left, cols_left, val);
+    else
+      tile_store(out, K, rows_left, cols_left, none, val, [](float* p, float v) { *p = v; });
   }
   asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
 }
@@ -399,9 +401,15 @@ hipError_t launch_tgemm_bwd_dw_parts(const uint16_t* dY, const uint16_t* X, int6
       if (e != hipSuccess) return e;
     }
   }
-  hipLaunchKernelGGL(tgemm_bwd_dw_kernel, dim3((unsigned)t.grid), dim3(256), 0, stream, dY, X, M,
-                     N, K, dW, accumulate, (uint32_t)tk, (uint32_t)t.full, (uint32_t)t.rem,
-                     (uint32_t)t.parts, t.per, slots);
+#define TM_DW_CASE(ACC_)                                                                          \
+  hipLaunchKernelGGL(tgemm_bwd_dw_kernel<ACC_>, dim3((unsigned)t.grid), dim3(256), 0, stream, dY, \
+                     X, M, N, K, dW, (uint32_t)tk, (uint32_t)t.full, (uint32_t)t.rem,             \
+                     (uint32_t)t.parts, t.per, slots)
+  if (accumulate)
+    TM_DW_CASE(true);
+  else
+    TM_DW_CASE(false);
+#undef TM_DW_CASE
   const hipError_t e = hipGetLastError();
   if (e != hipSuccess || t.parts == 1 || !slots) return e;
   return launch_reduce_parts(slots, t.rem, t.parts, ntiles - t.rem, tk, N, K, dW, false,

@@ -200,6 +200,20 @@ def test_float32_gradient_rounding():
     assert torch.equal(got[~nan].view(torch.int16), ref[~nan].view(torch.int16))
 
 
+# whole tiles (more than 256 of them) and cut ones, edges inside a block of 8
+# rows x 32 columns and at its end
+@pytest.mark.parametrize("M,N,K", [(3, 7648, 2368), (29, 9864, 2560), (90, 6456, 4160),
+                                   (129, 8512, 2048), (40, 264, 64)])
+def test_weight_grad_accumulates_in_one_sum(M, N, K):
+    print(f"[parts] dW accumulate M={M} N={N} K={K}", flush=True)
+    x, dy, _, _, _ = _operands(M, N, K, 64)
+    dyb = dy.to(torch.bfloat16)
+    old = torch.randn((N, K), device="cuda")
+    acc = old.clone()
+    ops.tgemm_bwd_dw_ste(dyb, x, acc, accumulate=True)
+    assert torch.equal(acc, old + ops.tgemm_bwd_dw_ste(dyb, x))
+
+
 # the forward's parts meet through tickets, and in slots; dX's and dW's in slots
 @pytest.mark.parametrize("M,N,K,g", [(4352, 4096, 512, 128), (2048, 8512, 2048, 128)])
 def test_scratch_in_graphs_and_on_two_streams(M, N, K, g):

@@ -58,7 +58,7 @@ def scratch(tmp_path_factory):
     *((f"tgemm_bwd_dx_f16_kernel<{g}, {out}, false>", 112)
       for g in (32, 64, 128, 256, 512) for out in ("true", "false")),
     *((f"tgemm_bwd_dx_f16_kernel<{g}, false, true>", 244) for g in (32, 64, 128, 256, 512)),
-    ("tgemm_bwd_dw_kernel", 160),
+    ("tgemm_bwd_dw_kernel<false>", 112), ("tgemm_bwd_dw_kernel<true>", 112),
     # <g, code stage, bfloat16 out, shape>: the forward's 256 x 256 and 64 x 128
     # tiles hold everything in registers
     *((f"tgemm_fwd_kernel<{g}, {ss}, {out}, {shape}>", most)
