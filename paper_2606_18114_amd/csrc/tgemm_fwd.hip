@@ -670,17 +670,24 @@ __global__ __launch_bounds__(64 * NW, fwd_waves(G, SS, MA)) void tgemm_fwd_kerne
   asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
 }
 
-// The three tile shapes, and per shape and group size: workgroups a CU holds
-// (0: not used); time of a 64-column stage with the chip full and with a CU's
-// workgroup alone on an idle chip (the first is set by the power cap and the
-// shared pipes, the second by a stage's own chain of waits).  Then what the
-// ways of joining parts cost: a slot's write and read and the reduction's
-// launch; the second pass of a ticket tile over Y.  Set so that the least
-// estimate is within 1.1% of the fastest on average (14% at worst) over 233
-// measured products (16 to 16384 tokens of ten layers from 3352 x 768 to 2048 x
-// 8192, g = 32 to 512) on every shape and cut.  At g = 32 the 128 x 128 tile is out: its two accumulators and four
-// scale steps a stage need more than the 256 registers (170 spilled; 4096 x
-// 2048 x 4096: 206 us, 64 x 128 tiles 92, 256 x 256 ones 98).
+// The three tile shapes, and per shape, group size and way of loading codes:
+// workgroups a CU holds (0: not used); time of a 64-column stage with the chip
+// full and with a CU's workgroup alone on an idle chip (the first is set by the
+// power cap and the shared pipes, the second by a stage's own chain of waits).
+// Then what the ways of joining parts cost: a slot's write and read and the
+// reduction's launch; the second pass of a ticket tile over Y.  Set so that the
+// least estimate is within 1.1% of the fastest on average (14% at worst) over
+// 233 measured products (16 to 16384 tokens of ten layers from 3352 x 768 to
+// 2048 x 8192, g = 32 to 512) on every shape and cut.  Where K is no multiple of
+// 256 each stage asks for 16 bytes of codes per row, and the small tiles do so
+// most often per output: those times are set by 576 products (32 to 20000
+// tokens, 256 to 12000 rows, 320 to 8192 columns), within 3.7% of the fastest
+// choice on average, 6.6% with the times above (414 x 10376 x 7040, g = 128: 137
+// us by those, 97 now; 18745 x 3535 x 3456, g = 64: 592 and 527; before the small
+// tiles 123 and 547).
+// At g = 32 the 128 x 128 tile is out: its two accumulators and four scale steps
+// a stage need more than the 256 registers (170 spilled; 4096 x 2048 x 4096: 206
+// us, 64 x 128 tiles 92, 256 x 256 ones 98).
 struct FwdShape {
   int bm, bn;
   double slot_us;
@@ -690,10 +697,15 @@ struct FwdStage {
   double full_us, alone_us;
 };
 constexpr FwdShape kFwdShapes[3] = {{256, 256, 0.079}, {128, 128, 0.024}, {64, 128, 0.009}};
-constexpr FwdStage kFwdStages[3][3] = {
-    {{1, 2.10, 1.96}, {0, 0.00, 0.00}, {2, 0.65, 0.46}},   // g = 32
-    {{1, 1.88, 1.74}, {2, 0.94, 0.87}, {3, 0.97, 0.27}},   // g = 64
-    {{1, 1.65, 1.40}, {2, 0.95, 0.63}, {3, 0.84, 0.30}}};  // g >= 128
+constexpr FwdStage kFwdStages[2][3][3] = {
+    // code stages of four (K % 256 == 0)
+    {{{1, 2.10, 1.96}, {0, 0.00, 0.00}, {2, 0.65, 0.46}},   // g = 32
+     {{1, 1.88, 1.74}, {2, 0.94, 0.87}, {3, 0.97, 0.27}},   // g = 64
+     {{1, 1.65, 1.40}, {2, 0.95, 0.63}, {3, 0.84, 0.30}}},  // g >= 128
+    // codes loaded stage by stage
+    {{{1, 2.38, 2.21}, {0, 0.00, 0.00}, {2, 0.82, 0.49}},   // g = 32
+     {{1, 2.43, 2.43}, {2, 1.27, 1.06}, {3, 1.44, 0.27}},   // g = 64
+     {{1, 1.56, 1.52}, {2, 0.99, 0.99}, {3, 1.11, 0.35}}}}; // g = 128
 constexpr double kFwdLaunchUs = 5.0, kFwdTileUs = 0.79, kFwdTicketUs = 0.064;
 
 // How the parts of a cut tile meet
@@ -738,7 +750,7 @@ static FwdPlan fwd_plan(int64_t M, int64_t N, int64_t K, int g, bool bf16_out) {
   double best_t = 0;
   for (int i = 0; i < 3; ++i) {
     const FwdShape& c = kFwdShapes[i];
-    const FwdStage& s = kFwdStages[g >= 128 ? 2 : g / 64][i];
+    const FwdStage& s = kFwdStages[K % 256 == 0 ? 0 : 1][g >= 128 ? 2 : g / 64][i];
     const int64_t tiles = ((M + c.bm - 1) / c.bm) * ((N + c.bn - 1) / c.bn);
     if (s.per_cu == 0 || tiles > 0x7FFFFFFF) continue;  // 32-bit tile numbers
     const int64_t P = (int64_t)cus * s.per_cu;

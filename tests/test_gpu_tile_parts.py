@@ -162,7 +162,11 @@ FORWARD = [(1, 64, 64, 32), (16, 256, 512, 128), (70, 1000, 320, 64), (300, 8512
            (33, 8512, 4096, 512), (2100, 4097, 192, 64),
            # leftover tiles after whole rounds: 64 and 48 (two parts in Y), 32
            (8192, 8512, 2048, 128), (6000, 8511, 1024, 32), (4096, 8512, 1408, 64),
-           (4096, 2048, 4096, 32)]
+           (4096, 2048, 4096, 32),
+           # K no multiple of 256 (stage times of its own in the plan): two parts in Y
+           # (slots in bfloat16), slots of small tiles, whole tiles of two shapes
+           (8192, 6344, 1408, 128), (40, 2056, 4160, 64), (2600, 2000, 1344, 64),
+           (414, 5377, 2112, 64)]
 
 
 @pytest.mark.parametrize("M,N,K,g", FORWARD)
