@@ -673,40 +673,42 @@ __global__ __launch_bounds__(64 * NW, fwd_waves(G, SS, MA)) void tgemm_fwd_kerne
 // The three tile shapes, and per shape, group size and way of loading codes:
 // workgroups a CU holds (0: not used); time of a 64-column stage with the chip
 // full and with a CU's workgroup alone on an idle chip (the first is set by the
-// power cap and the shared pipes, the second by a stage's own chain of waits).
-// Then what the ways of joining parts cost: a slot's write and read and the
-// reduction's launch; the second pass of a ticket tile over Y.  Set so that the
-// least estimate is within 1.1% of the fastest on average (14% at worst) over
+// power cap and the shared pipes, the second by a stage's own chain of waits);
+// time of a round's start and output.  Then what the ways of joining parts cost:
+// a slot's write and read and the reduction's launch; the second pass of a
+// ticket tile over Y.  Set so that the least estimate is within 1.1% of the fastest on average (14% at worst) over
 // 233 measured products (16 to 16384 tokens of ten layers from 3352 x 768 to
 // 2048 x 8192, g = 32 to 512) on every shape and cut.  Where K is no multiple of
 // 256 each stage asks for 16 bytes of codes per row, and the small tiles do so
-// most often per output: those times are set by 576 products (32 to 20000
-// tokens, 256 to 12000 rows, 320 to 8192 columns), within 3.7% of the fastest
-// choice on average, 6.6% with the times above (414 x 10376 x 7040, g = 128: 137
-// us by those, 97 now; 18745 x 3535 x 3456, g = 64: 592 and 527; before the small
-// tiles 123 and 547).
-// At g = 32 the 128 x 128 tile is out: its two accumulators and four scale steps
-// a stage need more than the 256 registers (170 spilled; 4096 x 2048 x 4096: 206
-// us, 64 x 128 tiles 92, 256 x 256 ones 98).
+// most often per output: those times are set by 567 products (32 to 20000
+// tokens, 128 to 12000 rows, 320 to 8192 columns), within 2.5% of the fastest
+// choice on average and 30% at worst; with the times above it was 4.7 and 42% at
+// g = 64 and 128 (414 x 10376 x 7040, g = 128: 137 us, now 95; 18745 x 3535 x
+// 3456, g = 64: 592 and 527; before the small tiles 123 and 547).
+// At g = 32 with code stages of four the 128 x 128 tile is out: its two
+// accumulators and four scale steps a stage need more than the 256 registers
+// (170 spilled; 4096 x 2048 x 4096: 206 us, 64 x 128 tiles 92, 256 x 256 ones
+// 98).  With codes stage by stage it has 220 and spills none (2459 x 3875 x
+// 8064: 212 us, 264 without it).
 struct FwdShape {
   int bm, bn;
   double slot_us;
 };
 struct FwdStage {
   int per_cu;
-  double full_us, alone_us;
+  double full_us, alone_us, tile_us;
 };
 constexpr FwdShape kFwdShapes[3] = {{256, 256, 0.079}, {128, 128, 0.024}, {64, 128, 0.009}};
 constexpr FwdStage kFwdStages[2][3][3] = {
     // code stages of four (K % 256 == 0)
-    {{{1, 2.10, 1.96}, {0, 0.00, 0.00}, {2, 0.65, 0.46}},   // g = 32
-     {{1, 1.88, 1.74}, {2, 0.94, 0.87}, {3, 0.97, 0.27}},   // g = 64
-     {{1, 1.65, 1.40}, {2, 0.95, 0.63}, {3, 0.84, 0.30}}},  // g >= 128
+    {{{1, 2.10, 1.96, 0.79}, {0, 0.00, 0.00, 0.00}, {2, 0.65, 0.46, 0.79}},   // g = 32
+     {{1, 1.88, 1.74, 0.79}, {2, 0.94, 0.87, 0.79}, {3, 0.97, 0.27, 0.79}},   // g = 64
+     {{1, 1.65, 1.40, 0.79}, {2, 0.95, 0.63, 0.79}, {3, 0.84, 0.30, 0.79}}},  // g >= 128
     // codes loaded stage by stage
-    {{{1, 2.38, 2.21}, {0, 0.00, 0.00}, {2, 0.82, 0.49}},   // g = 32
-     {{1, 2.43, 2.43}, {2, 1.27, 1.06}, {3, 1.44, 0.27}},   // g = 64
-     {{1, 1.56, 1.52}, {2, 0.99, 0.99}, {3, 1.11, 0.35}}}}; // g = 128
-constexpr double kFwdLaunchUs = 5.0, kFwdTileUs = 0.79, kFwdTicketUs = 0.064;
+    {{{1, 1.52, 1.52, 17.6}, {2, 0.91, 0.91, 6.18}, {3, 1.46, 0.41, 0.87}},   // g = 32
+     {{1, 1.35, 1.25, 21.5}, {2, 0.88, 0.80, 4.43}, {3, 1.35, 0.27, 0.41}},   // g = 64
+     {{1, 1.09, 1.04, 21.1}, {2, 0.95, 0.91, 4.37}, {3, 1.17, 0.35, 0.85}}}}; // g = 128
+constexpr double kFwdLaunchUs = 5.0, kFwdTicketUs = 0.064;
 
 // How the parts of a cut tile meet
 enum class FwdMeet { kWhole, kSlots, kTickets, kAtomics };
@@ -762,7 +764,7 @@ static FwdPlan fwd_plan(int64_t M, int64_t N, int64_t K, int g, bool bf16_out) {
       const double load = (double)(R * k) / (double)P;
       const double t = (double)(F * trips * unroll) * s.full_us +
                        (double)(run * unroll) * (s.alone_us + (s.full_us - s.alone_us) * load) +
-                       (double)(F + (R > 0)) * kFwdTileUs;
+                       (double)(F + (R > 0)) * s.tile_us;
       auto offer = [&](FwdMeet meet, double join_us) {
         if (best.grid != 0 && t + join_us >= best_t) return;
         best_t = t + join_us;
@@ -864,7 +866,7 @@ hipError_t launch_tgemm_fwd_parts(const uint16_t* X, const uint8_t* codes, const
       TM_FWD_B(GG, SS_, 4, 8);       \
     else if (p.shape == 2)           \
       TM_FWD_B(GG, SS_, 1, 4);       \
-    else if constexpr (GG >= 64)     \
+    else if constexpr (GG >= 64 || SS_ == 1) \
       TM_FWD_B(GG, SS_, 2, 4);       \
     else                             \
       return hipErrorInvalidValue;   \

@@ -166,7 +166,8 @@ FORWARD = [(1, 64, 64, 32), (16, 256, 512, 128), (70, 1000, 320, 64), (300, 8512
            # K no multiple of 256 (stage times of its own in the plan): two parts in Y
            # (slots in bfloat16), slots of small tiles, whole tiles of two shapes
            (8192, 6344, 1408, 128), (40, 2056, 4160, 64), (2600, 2000, 1344, 64),
-           (414, 5377, 2112, 64)]
+           (414, 5377, 2112, 64), (2459, 3875, 832, 32), (1822, 2475, 832, 32),
+           (700, 300, 1088, 32)]
 
 
 @pytest.mark.parametrize("M,N,K,g", FORWARD)
